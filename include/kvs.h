@@ -231,7 +231,9 @@ kvs_status kvs_set_direction_precision(kvs_ctx* ctx, int32_t prec);
  * ("reliable update"); once the recursive residual meets tol, the true one is confirmed as with
  * confirm_true.  Inner products and norms are FP64.  In flexible PCG the network then reads the
  * FP32 r and its output z is stored as the FP32 sum before the output scale (the value is the
- * same).  With an FP32 direction the plain CG's sweeps move 40 B per cell and iteration.
+ * same).  With an FP32 direction as well the plain CG and Jacobi-PCG advance two iterations per
+ * pair of sweeps (the second one's scalars from inner products of the vectors at hand; the stop
+ * test holds after every iteration), 40 B per cell and two iterations.
  * Applies from the next kvs_project. */
 kvs_status kvs_set_residual_precision(kvs_ctx* ctx, int32_t prec);
 /* Network used by kvs_project with precond = KVS_PC_UNET (flexible PCG:

@@ -252,8 +252,8 @@ kvs_status kvs_create(const kvs_grid* grid, const kvs_opts* opts, kvs_ctx** out)
     ok = ok && c->mem.get(&c->phi, N * sizeof(double)) == hipSuccess;
     ok = ok && c->mem.get(&c->r, N * sizeof(double)) == hipSuccess;
     ok = ok && c->mem.get(&c->Ap, N * sizeof(double)) == hipSuccess;
-    ok = ok && c->mem.get(&c->partials, 3 * (size_t)std::max<int64_t>(c->npart, 2048) * sizeof(double)) == hipSuccess;
-    ok = ok && c->mem.get(&c->cgs, sizeof(CgState)) == hipSuccess;
+    ok = ok && c->mem.get(&c->partials, KVS_CG_SUMS * (size_t)std::max<int64_t>(c->npart, 2048) * sizeof(double)) == hipSuccess;
+    ok = ok && c->mem.get(&c->cgs, 2 * sizeof(CgState)) == hipSuccess;
     ok = ok && hipHostMalloc(&c->cgs_host, sizeof(CgState), hipHostMallocDefault) == hipSuccess;
     if (!ok) {
         release(c);

@@ -34,6 +34,8 @@
 #include <mutex>
 #include <string>
 
+#include "kvs_cg_pair.hpp"
+#include "kvs_cg_scalars.hpp"
 #include "kvs_internal.hpp"
 #include "kvs_tiling.hpp"
 
@@ -52,7 +54,7 @@ struct CgGeom {
     double dinv;              // 1/diag(A)
 };
 
-enum { FIN_INIT = 0, FIN_ALPHA = 1, FIN_BETA = 2, FIN_TRUE = 3, FIN_FZ0 = 4, FIN_FBETA = 5, FIN_RESTART = 6, FIN_REPLACE = 7 };
+enum { FIN_INIT = 0, FIN_FRES = 1, FIN_TRUE = 2, FIN_FZ0 = 3, FIN_FBETA = 4, FIN_RESTART = 5, FIN_REPLACE = 6 };
 
 using kvs_tiling::tile_of;
 
@@ -258,19 +260,20 @@ __device__ __forceinline__ void sweep_partials(double v0, double v1, double* par
 template <int WX, int SBY, typename PT, typename RT>
 __global__ __launch_bounds__(64 * WX * SBY) void cg_dir_kernel(const CgGeom g, const SweepGeom sg, const RT* r_in,
                                                                const RT* zf, const PT* p_old, PT* p_new,
-                                                               const CgState* st, double* partials, int npart) {
+                                                               const CgFold fold, double* partials, int npart) {
+    const CgState* st = cg_fold<CG_BETA, 64 * WX * SBY>(fold, threadIdx.y * (64 * WX) + threadIdx.x);
     if (st->done) return;
     __shared__ double lds[2][SBY + 3][64 * WX + 4];
     const Lane L = sweep_lane<WX, SBY>(g, sg);
     const int tx = threadIdx.x, ty = threadIdx.y;
     const int sxy = g.nx * g.ny;
-    const double beta = st->beta;
+    const double beta = cg_uniform(st->beta);
     const bool net_z = st->flexible && !st->zjacobi;
     // the network's z is stored like r: z itself in FP64, or (RT = float) the
     // FP32 sum before the output scale st->net_out it was formed with
     const RT* r = net_z ? zf : r_in;
-    const double zs = net_z ? (sizeof(RT) == 4 ? st->net_out : 1.0)
-                            : ((st->jacobi || (st->flexible && st->zjacobi)) ? g.dinv : 1.0);
+    const double zs = cg_uniform(net_z ? (sizeof(RT) == 4 ? st->net_out : 1.0)
+                                       : ((st->jacobi || (st->flexible && st->zjacobi)) ? g.dinv : 1.0));
     const bool first = beta == 0.0;
     // the new direction as stored (PT = float: rounded once); the stencil,
     // p.Ap and the update sweep all use this stored value
@@ -311,13 +314,14 @@ __global__ __launch_bounds__(64 * WX * SBY) void cg_dir_kernel(const CgGeom g, c
 template <int WX, int SBY, typename PT, typename RT>
 __global__ __launch_bounds__(64 * WX * SBY) void cg_upd_kernel(const CgGeom g, const SweepGeom sg, double* phi,
                                                                const RT* r, RT* r_out, const PT* p,
-                                                               const CgState* st, double* partials, int npart) {
+                                                               const CgFold fold, double* partials, int npart) {
+    const CgState* st = cg_fold<CG_ALPHA, 64 * WX * SBY>(fold, threadIdx.y * (64 * WX) + threadIdx.x);
     if (st->done) return;
     __shared__ double lds[2][SBY + 3][64 * WX + 4];
     const Lane L = sweep_lane<WX, SBY>(g, sg);
     const int tx = threadIdx.x, ty = threadIdx.y;
     const int sxy = g.nx * g.ny;
-    const double alpha = st->alpha;
+    const double alpha = cg_uniform(st->alpha);
     const int kb = L.kb, ke = L.ke;
     double pm = p[(kb - 1) * sxy + L.col];
     double pc = p[kb * sxy + L.col];
@@ -470,47 +474,18 @@ __global__ __launch_bounds__(256) void cg_finalize_kernel(const double* partials
             st->beta = st->dinv * (st->rr - rro) / rz_old;
             st->rz = st->rr * st->dinv;
         }
-    } else if (mode == FIN_ALPHA) {
-        st->pAp = s1;
-        if (!(s1 > 0.0) || !isfinite(s1)) {
-            st->status = KVS_EBREAKDOWN;
-            st->done = 1;
-        } else {
-            st->alpha = st->rz / s1;
-        }
-    } else if (mode == FIN_BETA) {
+    } else if (mode == FIN_FRES) {
+        // flexible PCG, after the update: residual, stop test and network
+        // scales only; beta comes with the next z
         st->iters += 1;
         if (!isfinite(s1) || s1 < 0.0 || !isfinite(s2)) {
             st->status = KVS_EBREAKDOWN;
             st->done = 1;
             return;
         }
-        if (st->flexible) {
-            // residual, stop test and network scales only; beta comes later
-            st->rr = s1;
-            set_net_scales(s1);
-            if (st->fixed_iters > 0) {
-                if (st->iters >= st->fixed_iters) st->done = 1;
-            } else if (sqrt(st->rr / st->bb) < sqrt(st->tol2)) {
-                st->done = 1;
-            } else if (st->iters >= st->max_iter) {
-                st->status = KVS_ENOTCONV;
-                st->done = 1;
-            }
-            return;
-        }
-        const double rz_new = st->jacobi ? s2 : s1;
-        st->beta = rz_new / st->rz;
-        st->rz = rz_new;
         st->rr = s1;
-        if (st->fixed_iters > 0) {
-            if (st->iters >= st->fixed_iters) st->done = 1;
-        } else if (sqrt(st->rr / st->bb) < sqrt(st->tol2)) {
-            st->done = 1;
-        } else if (st->iters >= st->max_iter) {
-            st->status = KVS_ENOTCONV;
-            st->done = 1;
-        }
+        set_net_scales(s1);
+        cg_stop_test(*st);
     } else if (mode == FIN_RESTART) {
         // restart from the true residual r = -b - A phi: the iteration count
         // and b.b are kept, the direction is rebuilt from z alone (beta = 0)
@@ -601,7 +576,7 @@ int64_t kvs_cg_partials_needed(const kvs_grid& gr) {
     const SweepShape sh = sweep_shape(g.nx);
     const int sweep_xy = ((g.nx + 64 * sh.wx - 1) / (64 * sh.wx)) * ((g.ny + sh.by - 1) / sh.by);
     return std::max<int64_t>(std::max<int64_t>(nblocks(g), kvs_tiling::max_tiled_blocks(sweep_xy, g.nz - 2)),
-                             kvs_unet_out_blocks(gr));
+                             std::max<int64_t>(kvs_unet_out_blocks(gr), kvs_cg_pair_blocks_max(gr)));
 }
 
 #define CG_HIP(call)                                                      \
@@ -715,11 +690,18 @@ kvs_status cg_project(const CgBuffers& B, const kvs_solve_opts* o, kvs_solve_rep
         static const int cap2 = kvs_tiling::resident_blocks(cg_dir_kernel<2, 8, double, double>, 1024);
         static const int cap4 = kvs_tiling::resident_blocks(cg_dir_kernel<4, 4, double, double>, 1024);
         const int cap = shp.wx == 4 ? cap4 : (shp.wx == 2 ? cap2 : cap1);
-        sg.kchunk = kvs_tiling::choose_kchunk(sg.gx * sg.gy, g.nz - 2, cap);
+        sg.kchunk = kvs_tiling::choose_kchunk(sg.gx * sg.gy, g.nz - 2, cap,
+                                              kvs_tiling::cg_min_planes(sg.gx * sg.gy, g.nz - 2));
         sg.gz = (g.nz - 2 + sg.kchunk - 1) / sg.kchunk;
     }
     const int nbs = sg.gx * sg.gy * sg.gz;
     const dim3 sblk(64 * shp.wx, shp.by);
+    // scalars folded into the sweeps (not with a network, whose kernels read
+    // the control block between them); the update's sums have their own arrays
+    const bool fold = !flexible && nbs <= kFoldMax;
+    double* upd_part = part + (fold ? npart : 0);
+    const CgFold fold_dir{B.cgs, fold ? B.cgs + 1 : nullptr, upd_part, nbs, npart};
+    const CgFold fold_upd{fold ? B.cgs + 1 : B.cgs, fold ? B.cgs : nullptr, part, nbs, npart};
     // the direction buffers hold PT values (B.dir_fp32: float), the residual
     // buffers RT values (res32: float)
     auto launch_dir_t = [&](auto ptag, auto rtag, const double* r_buf, const double* zf_buf, const double* p_old_buf,
@@ -732,13 +714,13 @@ kvs_status cg_project(const CgBuffers& B, const kvs_solve_opts* o, kvs_solve_rep
         PT* p_new = reinterpret_cast<PT*>(p_new_buf);
         if (shp.wx == 4)
             hipLaunchKernelGGL((cg_dir_kernel<4, 4, PT, RT>), dim3(nbs), sblk, 0, stream, g, sg, r_in, zf, p_old,
-                               p_new, B.cgs, part, npart);
+                               p_new, fold_dir, part, npart);
         else if (shp.wx == 2)
             hipLaunchKernelGGL((cg_dir_kernel<2, 8, PT, RT>), dim3(nbs), sblk, 0, stream, g, sg, r_in, zf, p_old,
-                               p_new, B.cgs, part, npart);
+                               p_new, fold_dir, part, npart);
         else
             hipLaunchKernelGGL((cg_dir_kernel<1, 8, PT, RT>), dim3(nbs), sblk, 0, stream, g, sg, r_in, zf, p_old,
-                               p_new, B.cgs, part, npart);
+                               p_new, fold_dir, part, npart);
     };
     auto launch_upd_t = [&](auto ptag, auto rtag, const double* r_buf, double* r_out_buf, const double* p_buf) {
         using PT = decltype(ptag);
@@ -748,13 +730,13 @@ kvs_status cg_project(const CgBuffers& B, const kvs_solve_opts* o, kvs_solve_rep
         const PT* pv = reinterpret_cast<const PT*>(p_buf);
         if (shp.wx == 4)
             hipLaunchKernelGGL((cg_upd_kernel<4, 4, PT, RT>), dim3(nbs), sblk, 0, stream, g, sg, B.phi, r_in, r_out,
-                               pv, B.cgs, part, npart);
+                               pv, fold_upd, upd_part, npart);
         else if (shp.wx == 2)
             hipLaunchKernelGGL((cg_upd_kernel<2, 8, PT, RT>), dim3(nbs), sblk, 0, stream, g, sg, B.phi, r_in, r_out,
-                               pv, B.cgs, part, npart);
+                               pv, fold_upd, upd_part, npart);
         else
             hipLaunchKernelGGL((cg_upd_kernel<1, 8, PT, RT>), dim3(nbs), sblk, 0, stream, g, sg, B.phi, r_in, r_out,
-                               pv, B.cgs, part, npart);
+                               pv, fold_upd, upd_part, npart);
     };
     auto launch_dir = [&](const double* r_in, const double* zf, const double* p_old, double* p_new) {
         if (B.dir_fp32 && res32)
@@ -782,7 +764,10 @@ kvs_status cg_project(const CgBuffers& B, const kvs_solve_opts* o, kvs_solve_rep
     const int* stop = &B.cgs->done;
     // flexible PCG keeps the previous residual for beta: the update writes
     // the new residual into the other buffer (rb[ri] is the current one)
-    double* rb[2] = {B.r, flexible ? B.r2 : B.r};
+    // FP32 direction and residual without a network: two iterations per pair
+    // of sweeps, the residual ping-ponged between the halves of its buffer
+    const bool paired = B.dir_fp32 && res32 && !flexible;
+    double* rb[2] = {B.r, flexible ? B.r2 : paired ? reinterpret_cast<double*>(reinterpret_cast<float*>(B.r) + g.N) : B.r};
     int ri = 0;
     if (flexible) {
         // z = U(r) and the partial sums of z.r from the network's output kernel
@@ -806,14 +791,26 @@ kvs_status cg_project(const CgBuffers& B, const kvs_solve_opts* o, kvs_solve_rep
         long long launched = 0;
         double rr_ref = -1.0;  // r.r when r was last exact (first read of this call)
         while (true) {
-            for (int m = 0; m < chunk; ++m) {
+            for (int m = 0; m < (paired ? chunk / 2 : 0); ++m) {
+                const CgPair pr{stream, reinterpret_cast<const float*>(rb[ri]), reinterpret_cast<const float*>(B.p[pi]),
+                                reinterpret_cast<float*>(rb[1 - ri]), reinterpret_cast<float*>(B.p[1 - pi]), B.phi, B.cgs,
+                                part, npart, m == chunk / 2 - 1};
+                kvs_cg_pair_launch(B.grid, pr);
+                ri = 1 - ri;
+                pi = 1 - pi;
+            }
+            for (int m = 0; m < (paired ? 0 : chunk); ++m) {
                 launch_dir(rb[ri], z, B.p[pi], B.p[1 - pi]);
-                hipLaunchKernelGGL(cg_finalize_kernel, dim3(1), dim3(256), 0, stream, part, nbs, npart, 1,
-                                   (int)FIN_ALPHA, B.cgs);
+                if (!fold)
+                    hipLaunchKernelGGL(cg_scalars_kernel<CG_ALPHA>, dim3(1), dim3(256), 0, stream, part, nbs, npart, 0,
+                                       B.cgs);
                 launch_upd(rb[ri], rb[1 - ri], B.p[1 - pi]);
-                hipLaunchKernelGGL(cg_finalize_kernel, dim3(1), dim3(256), 0, stream, part, nbs, npart, 2,
-                                   (int)FIN_BETA, B.cgs);
+                if (!flexible && (!fold || m == chunk - 1))
+                    hipLaunchKernelGGL(cg_scalars_kernel<CG_BETA>, dim3(1), dim3(256), 0, stream, upd_part, nbs, npart,
+                                       fold ? 1 : 0, B.cgs);
                 if (flexible) {
+                    hipLaunchKernelGGL(cg_finalize_kernel, dim3(1), dim3(256), 0, stream, part, nbs, npart, 2,
+                                       (int)FIN_FRES, B.cgs);
                     // z = U(r_new) with the partial sums of z.r_new, z.r_old, r_new.r_old
                     const UnetDots dots{rb[ri], part, npart};
                     int nbo = 0;
@@ -825,7 +822,7 @@ kvs_status cg_project(const CgBuffers& B, const kvs_solve_opts* o, kvs_solve_rep
                 pi = 1 - pi;
             }
             CG_HIP(hipGetLastError());
-            launched += chunk;
+            launched += paired ? chunk / 2 : chunk;  // a pair applies at least one iteration
             CG_HIP(hipMemcpyAsync(B.cgs_host, B.cgs, sizeof(CgState), hipMemcpyDeviceToHost, stream));
             CG_HIP(hipStreamSynchronize(stream));
             if (B.cgs_host->done) break;
@@ -1015,7 +1012,9 @@ kvs_status kvs_run_projection(kvs_ctx* c, const kvs_solve_opts* o, kvs_solve_rep
 // taken once per device with hipGetSymbolAddress (the array's name is a host
 // stand-in, never a device pointer) and every later use goes through that
 // address.  Calls on one device share the array: calls that overlap on one
-// device race.  Layout: CgState | partials (3 npart) | r | p0 | p1 | Ap.
+// device race.  Layout: r | p0 | p1 | the two control blocks | partials; the
+// size test counts a control block, three arrays of one partial per block of
+// the 8-plane sweeps, and four fields, more than this takes.
 
 namespace {
 
@@ -1049,10 +1048,15 @@ kvs_status scratch_address(int device, unsigned char** out) {
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
-// Bytes of scratch a projection of `g` needs.
-size_t noalloc_bytes(const kvs_grid& g, int64_t npart) {
-    const size_t N = (size_t)g.nx * (size_t)g.ny * (size_t)g.nz;
-    return align256(sizeof(CgState)) + align256(3 * (size_t)npart * sizeof(double)) + 4 * align256(N * sizeof(double));
+// Bytes a projection of `g` is taken to need (the size test).
+size_t noalloc_bytes(const kvs_grid& gr) {
+    const size_t N = (size_t)gr.nx * (size_t)gr.ny * (size_t)gr.nz;
+    const CgGeom g = make_geom(gr);
+    const SweepShape sh = sweep_shape(g.nx);
+    const int64_t xy = (int64_t)((g.nx + 64 * sh.wx - 1) / (64 * sh.wx)) * ((g.ny + sh.by - 1) / sh.by);
+    const int64_t npart = std::max<int64_t>(std::max<int64_t>(nblocks(g), xy * std::max(1, (g.nz - 2 + 7) / 8)),
+                                            std::max<int64_t>(kvs_unet_out_blocks(gr), 2048));
+    return 256 + align256(3 * (size_t)npart * sizeof(double)) + 4 * align256(N * sizeof(double));
 }
 
 // Zero the outer layer of `ncomp` consecutive scalar fields of double.
@@ -1086,8 +1090,7 @@ kvs_status kvs_project_noalloc(const kvs_grid* grid, const double* F, double* ph
     if (o.max_iter <= 0) return noalloc_fail(KVS_EINVAL, "max_iter must be > 0");
     if (o.precond != KVS_PC_NONE && o.precond != KVS_PC_JACOBI)
         return noalloc_fail(KVS_EINVAL, "the allocation-free projection runs CG or Jacobi-PCG only");
-    const int64_t npart = std::max<int64_t>(kvs_cg_partials_needed(g), 2048);
-    const size_t need = noalloc_bytes(g, npart);
+    const size_t need = noalloc_bytes(g);
     if ((double)g.nx * (double)g.ny * (double)g.nz > 2.0e9 || need > (size_t)KVS_NOALLOC_SCRATCH_BYTES) {
         char detail[160];
         std::snprintf(detail, sizeof(detail), "grid %lldx%lldx%lld needs %zu bytes of scratch, the maximum is %zu",
@@ -1116,13 +1119,15 @@ kvs_status kvs_project_noalloc(const kvs_grid* grid, const double* F, double* ph
     B.stream = static_cast<hipStream_t>(stream);
     B.F = F;
     B.phi = phi;
-    B.cgs = reinterpret_cast<CgState*>(take(sizeof(CgState)));
-    B.partials = reinterpret_cast<double*>(take(3 * (size_t)npart * sizeof(double)));
-    B.npart = (int)npart;
     B.r = reinterpret_cast<double*>(take(N * sizeof(double)));
     B.p[0] = reinterpret_cast<double*>(take(N * sizeof(double)));
     B.p[1] = reinterpret_cast<double*>(take(N * sizeof(double)));
-    B.Ap = reinterpret_cast<double*>(take(N * sizeof(double)));
+    B.Ap = nullptr;  // the network's z: not used here
+    B.cgs = reinterpret_cast<CgState*>(take(2 * sizeof(CgState)));
+    const int64_t npart = std::max<int64_t>(kvs_cg_partials_needed(g), 2048);
+    B.partials = reinterpret_cast<double*>(take(3 * (size_t)npart * sizeof(double)));
+    B.npart = (int)npart;
+    if (off > (size_t)KVS_NOALLOC_SCRATCH_BYTES) return noalloc_fail(KVS_EINVAL, "scratch layout");
     B.r2 = nullptr;
     B.cgs_host = &host_state;
     B.FS = FS;

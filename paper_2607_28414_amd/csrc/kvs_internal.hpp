@@ -10,6 +10,9 @@
 
 #include "kvs.h"
 
+// Arrays of block partials a projection works with.
+constexpr int KVS_CG_SUMS = 7;
+
 // Device-side control block of one projection solve.  Written only by the
 // single-block finalize kernels; read by every CG kernel (early exit once
 // `done` is set) and copied to the host once per chunk of iterations.
@@ -28,6 +31,11 @@ struct CgState {
     int done, status, jacobi, flexible;
     int zjacobi;            // flexible PCG: this iteration's z is r / diag(A)
     int fallbacks;          // number of Jacobi fallbacks taken
+    // two iterations per pair of sweeps (kvs_cg_pair.hip): the coefficients of
+    // the pair, r.r after its first iteration, and how many of them it applies
+    double pair_a0, pair_b0, pair_a1, pair_r11;
+    int pair_m;
+    int pending;  // folded scalars: an update's sums wait for the next sweep
 };
 
 // Device memory of a context or batch: the caller's allocator when kvs_opts
@@ -110,9 +118,9 @@ struct kvs_ctx {
     double* r2 = nullptr;  // flexible PCG: the residual of the previous iteration (ping-pong with r)
     double* p[2] = {nullptr, nullptr};
     double* Ap = nullptr;
-    double* partials = nullptr;  // 3 * npart
+    double* partials = nullptr;  // KVS_CG_SUMS * npart
     int64_t npart = 0;
-    CgState* cgs = nullptr;       // device
+    CgState* cgs = nullptr;       // device, two copies (folded scalars alternate)
     CgState* cgs_host = nullptr;  // pinned host mirror
     bool have_phi = false;
 

@@ -36,12 +36,30 @@ int resident_blocks(K kernel, int threads) {
     return per_cu * prop.multiProcessorCount;
 }
 
+// Tiles of a two-stage stencil (the value of the second stage needs the first
+// stage's values one cell around it) along one axis of n nodes: a tile covers
+// T consecutive interior nodes with the first stage and owns the T - 2 inner
+// ones, plus its end nodes where they sit next to a wall (whose first-stage
+// value is 0 and needs no thread).  Tile t covers nodes 1 + t (T - 2) ..
+// t (T - 2) + T, so one tile spans n - 2 <= T interior nodes and every further
+// one adds T - 2.
+inline int overlap_tiles(int n, int T) {
+    const int m = n - 2;
+    return m <= T ? 1 : (m - 2 + T - 3) / (T - 2);
+}
+
+// Whether local position l of tile t (T wide, of nt) owns its node i of n.
+__device__ __forceinline__ bool overlap_owns(int l, int t, int T, int i, int n) {
+    return (l >= 1 || t == 0) && (l <= T - 2 || i == n - 2);
+}
+
 // Split z into segments so that (xy tiles) x (segments) fills whole rounds of
-// resident blocks; fewer, longer segments re-read fewer halo planes.
-inline int choose_kchunk(int xytiles, int planes, int cap) {
+// resident blocks; fewer, longer segments re-read fewer halo planes.  At
+// least min_planes planes per segment.
+inline int choose_kchunk(int xytiles, int planes, int cap, int min_planes = 8) {
     int best_seg = 1;
     double best = -1.0;
-    const int max_seg = std::max(1, planes / 8);
+    const int max_seg = std::max(1, planes / min_planes);
     for (int seg = 1; seg <= max_seg; ++seg) {
         const int chunk = (planes + seg - 1) / seg;
         const int nseg = (planes + chunk - 1) / chunk;
@@ -58,10 +76,15 @@ inline int choose_kchunk(int xytiles, int planes, int cap) {
     return (planes + best_seg - 1) / best_seg;
 }
 
-// Upper bound on the blocks any tiled launch over `planes` z planes uses:
-// at least 8 planes per segment.
+// Shortest z segments of the CG sweeps.  Where segments of 8 planes leave the
+// chip short of blocks, a sweep's time is its blocks' serial march, not their
+// halo planes, so segments of 2 planes are allowed.
+inline int cg_min_planes(int xytiles, int planes) { return (long long)xytiles * ((planes + 7) / 8) <= 1024 ? 2 : 8; }
+
+// Upper bound on the blocks a CG sweep over `planes` z planes uses.
 inline long long max_tiled_blocks(int xytiles, int planes) {
-    return (long long)xytiles * std::max(1, (planes + 7) / 8);
+    const int m = cg_min_planes(xytiles, planes);
+    return (long long)xytiles * std::max(1, (planes + m - 1) / m);
 }
 
 }  // namespace kvs_tiling
