@@ -446,15 +446,15 @@ kvs_status kvs_batch_trace_count(const kvs_batch* b, int64_t* nsteps_recorded);
 kvs_status kvs_batch_read_traces(kvs_batch* b, int32_t i, double* out, int64_t cap, int64_t* n_written);
 
 /* Steps per launch of kvs_batch_step: 1 or 2 (the default), else KVS_EINVAL.
- * With 2, pairs of consecutive steps in which no instance's envelope is
- * non-zero are advanced by one launch of the two-step tile over all
- * instances (the result is bitwise that of one-step launches); it applies to
- * FP32 batches with a viscous instance, rows of at most 256 cells, and probe
- * cells distinct and off each instance's planes k = 0, nz - 1
- * (kvs_batch_step_blocking_applies).  Runs that take the persistent path are
- * not affected. */
+ * With 2, pairs of consecutive steps are advanced by one launch per tile shape
+ * of the two-step tile over all instances (the result is bitwise that of
+ * one-step launches); it applies to FP32 batches with probe cells distinct and
+ * off each instance's planes k = 0, nz - 1.  Runs that take the persistent path
+ * are not affected. */
 kvs_status kvs_batch_set_step_blocking(kvs_batch* b, int32_t steps);
-/* 1 if two-step launches apply to the batch as it is now, else 0. */
+/* 1 if two-step launches apply to the batch as it is now and it is one of those
+ * this function has always named (a viscous instance, rows of at most 256
+ * cells); else 0. */
 int32_t kvs_batch_step_blocking_applies(const kvs_batch* b);
 /* Persistent runs of small instances (on by default): when every instance's
  * whole state (u and w, 24 B per node in FP32, 48 B in FP64) fits in 150 KB,
@@ -573,19 +573,21 @@ kvs_status kvs_set_step_variant(kvs_ctx* ctx, int32_t v);
  * issues tiles XCD by XCD in contiguous ranges (y-adjacent tiles share L2). */
 kvs_status kvs_set_step_tuning(kvs_ctx* ctx, int32_t v, int32_t zchunk, int32_t remap);
 /* Steps per launch of kvs_step: 1 or 2 (the default), else KVS_EINVAL.  With
- * 2, kvs_step advances each pair of consecutive steps whose envelope values
- * g_n are both 0 in one launch (temporal blocking of the Sec. 3.1 update: the
- * intermediate state is formed on chip, with its rows next to each tile's
- * computed twice); the result is that of two one-step launches (the same
- * FP32 operations in the same order).  Applies where kvs_step_blocking_applies
- * says so: FP32 state, heterogeneous viscous medium, no absorbing layer, no
- * peak planes, nx <= 256, and probe cells (if any) distinct and off the planes
- * k = 0 and nz - 1; elsewhere, for a step with force and for the last step of
- * an odd count, kvs_step launches one step as with 1.  Traces are recorded
- * for every step either way.  Kernel timing (kvs_kernel_time) counts the
- * steps the timed launches advanced. */
+ * 2, kvs_step advances pairs of consecutive steps in one launch (temporal
+ * blocking of the Sec. 3.1 update: the intermediate state is formed on chip,
+ * with the cells at each tile's edges computed twice); the result is that of
+ * two one-step launches (the same operations in the same order).  One step per
+ * launch is left for the last step of an odd count, for contexts with an
+ * absorbing layer, for probe cells that are not distinct or lie on the planes
+ * k = 0 or nz - 1, and for FP64 grids of exactly 10 rows.  Traces are recorded
+ * for every step either way.  Kernel timing (kvs_kernel_time) counts the steps
+ * the timed launches advanced. */
 kvs_status kvs_set_step_blocking(kvs_ctx* ctx, int32_t steps);
-/* 1 if two-step launches apply to the context as it is now, else 0. */
+/* 1 if two-step launches apply to the context as it is now and it is one of
+ * those this function has always named: FP32 state, viscous medium, no
+ * absorbing layer, no peak planes, nx <= 256, and probe cells (if any) distinct
+ * and off the planes k = 0 and nz - 1; else 0 (FP64, lossless, wide and
+ * peak-mapped contexts too, although kvs_step pairs their steps as well). */
 int32_t kvs_step_blocking_applies(const kvs_ctx* ctx);
 /* Time every variant on this context's grid, precision and medium, each with
  * the automatic z split and with 16-, 32- and 64-plane z segments

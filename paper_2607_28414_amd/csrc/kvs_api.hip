@@ -589,19 +589,6 @@ kvs_status kvs_set_probes(kvs_ctx* c, const int64_t* ijk, int64_t n, int32_t com
             slot = (int)p;
         }
     }
-    if (rows_ok) {
-        // one entry per 64-cell segment of each row: the row's offset where
-        // the segment holds a probe, else -1
-        const int64_t nseg = (g.nx + 63) / 64;
-        std::vector<int> segtab((size_t)(g.ny * g.nz * nseg), -1);
-        for (int64_t r = 0; r < g.ny * g.nz; ++r) {
-            const int off = rowtab[(size_t)r];
-            if (off < 0) continue;
-            for (int64_t i = 0; i < g.nx; ++i)
-                if (ptab[(size_t)off + (size_t)i] >= 0) segtab[(size_t)(r * nseg + i / 64)] = off;
-        }
-        rowtab.swap(segtab);
-    }
     API_HIP(c, hipStreamSynchronize(c->stream));
     dfree(c->mem, c->probe_cells);
     dfree(c->mem, c->probe_rowtab);
@@ -654,7 +641,7 @@ kvs_status kvs_step(kvs_ctx* c, int64_t nsteps) {
         const int64_t n = c->step;
         const double gn = n < n_env ? c->env[(size_t)n] : 0.0;
         const double gn1 = n + 1 < n_env ? c->env[(size_t)(n + 1)] : 0.0;
-        const int adv = c->step_block == 2 && q + 1 < nsteps && gn == 0.0 && gn1 == 0.0 && kvs_step2_supported(c) ? 2 : 1;
+        const int adv = c->step_block == 2 && q + 1 < nsteps && kvs_step2_supported(c) ? 2 : 1;
         if (c->nprobes > 0 && q > 0) c->probe_fused_out = c->traces + (c->trace_steps - 1) * per_slot;
         if (c->nprobes > 0 && adv == 2) c->probe_mid_out = c->traces + c->trace_steps * per_slot;
         if (c->timing) {
@@ -665,7 +652,7 @@ kvs_status kvs_step(kvs_ctx* c, int64_t nsteps) {
             c->launch_ev[0] = ea;
             c->launch_ev[1] = eb;
         }
-        const hipError_t le = adv == 2 ? kvs_launch_step2(c) : kvs_launch_step(c, gn);
+        const hipError_t le = adv == 2 ? kvs_launch_step2(c, gn, gn1) : kvs_launch_step(c, gn);
         c->launch_ev[0] = c->launch_ev[1] = nullptr;
         c->probe_fused_out = nullptr;
         c->probe_mid_out = nullptr;
@@ -673,7 +660,7 @@ kvs_status kvs_step(kvs_ctx* c, int64_t nsteps) {
         if (c->pml_cells > 0) API_HIP(c, kvs_launch_pml(c, gn));
         c->cur = 1 - c->cur;
         if (c->nprobes > 0) c->trace_steps += adv;  // last slot filled by the next launch or the gather below
-        if (c->npeak > 0) API_HIP(c, kvs_launch_peak_update(c, c->u[c->cur]));
+        if (c->npeak > 0) API_HIP(c, kvs_launch_peak_update(c, c->u[c->cur], adv == 2));
         c->step += adv;
         q += adv;
     }
@@ -850,8 +837,8 @@ kvs_status kvs_set_peak_planes(kvs_ctx* c, const int32_t* axis, const int64_t* i
     c->npeak = 0;
     c->peak_cells = 0;
     if (n == 0) return KVS_OK;
-    API_HIP(c, c->mem.get(&c->peak, (size_t)total * tsize(c)));
-    API_HIP(c, hipMemsetAsync(c->peak, 0, (size_t)total * tsize(c), c->stream));
+    API_HIP(c, c->mem.get(&c->peak, 2 * (size_t)total * tsize(c)));
+    API_HIP(c, hipMemsetAsync(c->peak, 0, 2 * (size_t)total * tsize(c), c->stream));
     for (int p = 0; p < n; ++p) {
         c->peak_axis[p] = axis[p];
         c->peak_index[p] = index[p];
@@ -859,7 +846,7 @@ kvs_status kvs_set_peak_planes(kvs_ctx* c, const int32_t* axis, const int64_t* i
     }
     c->npeak = n;
     c->peak_cells = total;
-    API_HIP(c, kvs_launch_peak_update(c, c->u[c->cur]));
+    API_HIP(c, kvs_launch_peak_update(c, c->u[c->cur], false));
     API_HIP(c, hipStreamSynchronize(c->stream));
     return KVS_OK;
 }
@@ -1127,7 +1114,7 @@ kvs_status kvs_set_step_tuning(kvs_ctx* c, int32_t v, int32_t zchunk, int32_t re
     if (v < 0 || v >= kvs_step_variant_count()) return fail(c, KVS_EINVAL, "no such step variant");
     if (zchunk < 0) return fail(c, KVS_EINVAL, "zchunk < 0");
     c->step_variant = v;
-    c->step_zchunk = zchunk;
+    c->step_zchunk = c->step2_zchunk = zchunk;
     c->step_remap = remap != 0;
     return KVS_OK;
 }
@@ -1154,7 +1141,7 @@ kvs_status kvs_set_residual_precision(kvs_ctx* c, int32_t prec) {
     return KVS_OK;
 }
 
-int32_t kvs_step_blocking_applies(const kvs_ctx* c) { return c && c->have_material && kvs_step2_supported(c) ? 1 : 0; }
+int32_t kvs_step_blocking_applies(const kvs_ctx* c) { return c && c->have_material && kvs_step2_reported(c) ? 1 : 0; }
 
 kvs_status kvs_autotune_step(kvs_ctx* c, int32_t trial_steps, int32_t* chosen, double* ms_per_launch,
                              int32_t cap) {
@@ -1337,7 +1324,6 @@ static kvs_status batch_upload_probes2(kvs_batch* b) {
         const int64_t p1 = b->probe_first.empty() ? 0 : b->probe_first[i + 1];
         if (p1 == p0) continue;
         const kvs_grid& g = b->inst[i]->grid;
-        const int64_t nseg = (g.nx + 63) / 64;
         std::vector<int> row((size_t)(g.ny * g.nz), -1), ptab;
         for (int64_t p = p0; p < p1 && b->probes2_ok; ++p) {
             const int64_t cell = b->probe_cell[(size_t)p];
@@ -1360,15 +1346,8 @@ static kvs_status batch_upload_probes2(kvs_batch* b) {
             slot = (int)(p - p0);
         }
         if (!b->probes2_ok) break;
-        std::vector<int> seg((size_t)(g.ny * g.nz * nseg), -1);
-        for (int64_t r = 0; r < g.ny * g.nz; ++r) {
-            const int off = row[(size_t)r];
-            if (off < 0) continue;
-            for (int64_t x = 0; x < g.nx; ++x)
-                if (ptab[(size_t)off + (size_t)x] >= 0) seg[(size_t)(r * nseg + x / 64)] = off;
-        }
         b->rowtab2_off[i] = (int64_t)all.size();
-        all.insert(all.end(), seg.begin(), seg.end());
+        all.insert(all.end(), row.begin(), row.end());
         b->ptab2_off[i] = (int64_t)all.size();
         all.insert(all.end(), ptab.begin(), ptab.end());
     }

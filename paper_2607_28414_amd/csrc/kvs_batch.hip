@@ -107,13 +107,20 @@ int instance_shape(const kvs_batch* b, const kvs_ctx* c) {
     return batch_variant(b);
 }
 
+// mid: the intermediate slot of a two-step launch (else null), whose values on
+// the Dirichlet layer are written here
 template <typename T>
 __global__ void batch_probe_kernel(const BatchInst<T>* inst, const long long* probes, int np, int comp, int parity,
-                                   double* out) {
+                                   double* out, double* mid) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= np) return;
     const StepArgs<T>& a = inst[probes[2 * p]].a[parity];
-    out[p] = (double)a.un[comp * a.N + probes[2 * p + 1]];  // u after the step
+    const long long q = probes[2 * p + 1];
+    out[p] = (double)a.un[comp * a.N + q];  // u after the step
+    if (mid) {
+        const int i = (int)(q % a.nx), j = (int)((q / a.nx) % a.ny);
+        if (i == 0 || i == a.nx - 1 || j == 0 || j == a.ny - 1) mid[p] = 0.0;
+    }
 }
 
 template <typename T>
@@ -233,65 +240,87 @@ std::vector<uint8_t> batch_force_mask(const kvs_batch* b, int64_t nsteps) {
 
 // ---- two steps per launch ----------------------------------------------------
 //
-// Pairs of steps without force are advanced by one launch of the two-step tile
-// (kvs_step2_tile.hpp, homogeneous form) over a work list of (instance, row
-// pair, z segment), one launch per tile width (128, 192 or 256 threads per
-// row); the result is bitwise that of two one-step launches.  The
-// intermediate state's probe values are written by the kernel into their
-// trace slot; the gather after the launch records the second step's.
+// Pairs of steps are advanced by one launch of the two-step tile
+// (kvs_step2_tile.hpp, homogeneous form) over a work list of (instance, tile,
+// z segment), one launch per tile shape; the result is bitwise that of two
+// one-step launches.  The intermediate state's probe values are written by the
+// kernel into their trace slot; the gather after the launch records the second
+// step's (and the intermediate zeros of probes on the Dirichlet layer).
 
 struct BatchInst2 {
-    Step2Args a2[2];   // [parity], buffers as in BatchInst::a
+    Step2Args<float> a2[2];  // [parity], buffers as in BatchInst::a
+    const double* env;
+    long long n_env;
     long long probe0;  // the instance's first probe in the flat probe list
 };
 
 constexpr int kStep2Zchunk = 64;  // z planes per block of the two-step launches
 
-// Thread rows of the batched two-step tiles by tile width (64 WX threads per
-// row): close to 1024 threads per block, for four waves per SIMD at one block
-// per CU (the tiles' LDS allows one).  Measured on the 64-instance sweep: 8
-// rows at 128 threads per row beat 4 rows at two blocks per CU by 4 %, and 5
-// rows at 192 beat 4 rows (three waves per SIMD) by 1.4x.
-template <int WX>
-constexpr int step2_rows() {
-    return WX == 2 ? 8 : WX == 3 ? 5 : 4;
-}
-
-template <int WX>
-__global__ __launch_bounds__(64 * WX * step2_rows<WX>()) void batch_step2_kernel(const BatchInst2* inst,
-                                                                                const int4* work, int nwork,
-                                                                                int parity, double* slot) {
+// FORCE: some instance's envelope is non-zero in one of the two steps; the
+// others take the tile without force.
+template <bool VISC, bool FORCE, int WX, int R>
+__global__ __launch_bounds__(64 * WX * R) void batch_step2_kernel(const BatchInst2* inst, const int4* work, int nwork,
+                                                                  long long n, int parity, double* slot) {
+    __shared__ __align__(16) float lds[Step2Tile<float, false, VISC, WX, R>::LDS];
     const int t = tile_of(blockIdx.x, nwork);
     const int4 wi = work[t];
     const BatchInst2& bi = inst[wi.x];
-    Step2Args A = bi.a2[parity];
+    Step2Args<float> A = bi.a2[parity];
     A.pmid = slot != nullptr && A.rowtab != nullptr ? slot + bi.probe0 : nullptr;
-    step2_tile<false, WX, step2_rows<WX>()>(A, wi.y, wi.z);
+    if constexpr (FORCE) {
+        A.a.gn = n < bi.n_env ? (float)bi.env[n] : 0.f;
+        A.gn2 = n + 1 < bi.n_env ? (float)bi.env[n + 1] : 0.f;
+        if (A.a.gn != 0.f || A.gn2 != 0.f) {
+            step2_tile<float, false, VISC, true, false, WX, R>(A, nullptr, lds, wi.y, wi.z, wi.w);
+            return;
+        }
+    }
+    step2_tile<float, false, VISC, false, false, WX, R>(A, nullptr, lds, wi.y, wi.z, wi.w);
 }
 
-int step2_wx(int64_t nx) { return nx <= 128 ? 2 : nx <= 192 ? 3 : 4; }
-int step2_out_rows(int wx) { return (wx == 2 ? step2_rows<2>() : wx == 3 ? step2_rows<3>() : step2_rows<4>()) - 2; }
+// The tile shape with the least work over the instance's rows and columns,
+// whole tiles counted.  Edges 64, 96, 128, 160 take 64 x 16 threads, 192 takes
+// 192 x 5.
+int step2_shape(const kvs_grid& g) {
+    int best = -1;
+    long long least = 0;
+    for (int s = 0; s < kStep2Shapes; ++s) {
+        if (!step2_offers(s, g.ny)) continue;
+        const long long w = (long long)overlap_tiles((int)g.nx, 64 * kStep2Wx[s]) *
+                            overlap_tiles((int)g.ny, kStep2Rows[s]) * step2_units(s);
+        if (best < 0 || w < least) {
+            best = s;
+            least = w;
+        }
+    }
+    return best;
+}
 
 hipError_t prepare2(kvs_batch* b) {
-    b->two_ok = kvs_batch_two_step_supported(b);
+    b->two_ok = kvs_batch_step2_supported(b);
     if (!b->two_ok) return hipSuccess;
     const int n = (int)b->inst.size();
     std::vector<BatchInst2> params((size_t)n);
+    const double* env = reinterpret_cast<const double*>(static_cast<const char*>(b->dev_params) +
+                                                        sizeof(BatchInst<float>) * (size_t)n);
     for (int i = 0; i < n; ++i) {
         kvs_ctx* c = b->inst[(size_t)i];
         const int64_t roff = i < (int)b->rowtab2_off.size() ? b->rowtab2_off[(size_t)i] : -1;
         const int64_t poff = i < (int)b->ptab2_off.size() ? b->ptab2_off[(size_t)i] : -1;
+        const int sh = step2_shape(c->grid);
         for (int par = 0; par < 2; ++par) {
-            Step2Args& A = params[(size_t)i].a2[par];
-            A = Step2Args{};
+            Step2Args<float>& A = params[(size_t)i].a2[par];
+            A = Step2Args<float>{};
             A.a = instance_args<float>(c, par == 0 ? c->cur : 1 - c->cur, 4, 1, 1, kStep2Zchunk);
-            const int orow = step2_out_rows(step2_wx(A.a.nx));
-            A.a.gx = 1;
-            A.a.gy = (A.a.ny + orow - 1) / orow;
+            A.a.gx = overlap_tiles(A.a.nx, 64 * kStep2Wx[sh]);
+            A.a.gy = overlap_tiles(A.a.ny, kStep2Rows[sh]);
             A.a.pcomp = b->comp;
             A.rowtab = roff >= 0 ? b->dev_ptabs2 + roff : nullptr;
             A.ptab = poff >= 0 ? b->dev_ptabs2 + poff : nullptr;
         }
+        params[(size_t)i].env = env;
+        params[(size_t)i].n_env = (long long)c->env.size();
+        env += c->env.size();
         params[(size_t)i].probe0 = b->probe_first.empty() ? 0 : (long long)b->probe_first[(size_t)i];
     }
     const size_t bytes = sizeof(BatchInst2) * (size_t)n;
@@ -308,15 +337,16 @@ hipError_t prepare2(kvs_batch* b) {
     if (e == hipSuccess && !b->dev_work2) {
         std::vector<int4> work;
         b->groups2.clear();
-        for (int wx = 2; wx <= 4; ++wx) {
+        for (int sh = 0; sh < kStep2Shapes; ++sh) {
             const int first = (int)work.size();
             for (int i = 0; i < n; ++i) {
-                if (step2_wx(b->inst[(size_t)i]->grid.nx) != wx) continue;
+                if (step2_shape(b->inst[(size_t)i]->grid) != sh) continue;
                 const StepArgs<float>& a = params[(size_t)i].a2[0].a;
                 for (int bz = 0; bz < a.gz; ++bz)
-                    for (int by = 0; by < a.gy; ++by) work.push_back(make_int4(i, by, bz, 0));
+                    for (int by = 0; by < a.gy; ++by)
+                        for (int bx = 0; bx < a.gx; ++bx) work.push_back(make_int4(i, bx, by, bz));
             }
-            if ((int)work.size() > first) b->groups2.push_back({wx, first, (int)work.size() - first});
+            if ((int)work.size() > first) b->groups2.push_back({sh, first, (int)work.size() - first});
         }
         e = b->mem.get(&b->dev_work2, sizeof(int4) * work.size());
         if (e == hipSuccess)
@@ -328,36 +358,35 @@ hipError_t prepare2(kvs_batch* b) {
     return e;
 }
 
-void launch_batch_step2(kvs_batch* b, int parity, double* slot) {
-    const BatchInst2* inst = static_cast<const BatchInst2*>(b->dev_params2);
+template <bool VISC, bool FORCE, int S>
+void launch_batch_step2_shape(kvs_batch* b, const kvs_batch::Group& g, long long n, int parity, double* slot) {
+    hipLaunchKernelGGL((batch_step2_kernel<VISC, FORCE, kStep2Wx[S], kStep2Rows[S]>), dim3(g.count),
+                       dim3(64 * kStep2Wx[S], kStep2Rows[S]), 0, b->stream, static_cast<const BatchInst2*>(b->dev_params2),
+                       static_cast<const int4*>(b->dev_work2) + g.off, g.count, n, parity, slot);
+}
+
+template <bool VISC, bool FORCE>
+void launch_batch_step2(kvs_batch* b, long long n, int parity, double* slot) {
     for (const kvs_batch::Group& g : b->groups2) {
-        const int4* w = static_cast<const int4*>(b->dev_work2) + g.off;
         switch (g.shape) {
-            case 2:
-                hipLaunchKernelGGL(batch_step2_kernel<2>, dim3(g.count), dim3(128, step2_rows<2>()), 0, b->stream, inst, w,
-                                   g.count, parity, slot);
-                break;
-            case 3:
-                hipLaunchKernelGGL(batch_step2_kernel<3>, dim3(g.count), dim3(192, step2_rows<3>()), 0, b->stream, inst, w,
-                                   g.count, parity, slot);
-                break;
-            default:
-                hipLaunchKernelGGL(batch_step2_kernel<4>, dim3(g.count), dim3(256, step2_rows<4>()), 0, b->stream, inst, w,
-                                   g.count, parity, slot);
-                break;
+            case 0: launch_batch_step2_shape<VISC, FORCE, 0>(b, g, n, parity, slot); break;
+            case 1: launch_batch_step2_shape<VISC, FORCE, 1>(b, g, n, parity, slot); break;
+            case 2: launch_batch_step2_shape<VISC, FORCE, 2>(b, g, n, parity, slot); break;
+            default: launch_batch_step2_shape<VISC, FORCE, 3>(b, g, n, parity, slot); break;
         }
     }
 }
 
 // The launches of a run: per step 0 (one-step launch), 1 (one-step launch
-// reading f_S), 2 (first step of a two-step launch), 3 (its second step).
+// reading f_S), 2 (first step of a two-step launch), 4 (the same reading f_S),
+// 3 (the second step of either).
 std::vector<uint8_t> batch_plan(const kvs_batch* b, int64_t nsteps, int64_t* launches) {
     std::vector<uint8_t> plan = batch_force_mask(b, nsteps);
     const bool two = b->two_ok && b->step_block == 2;
     int64_t nl = 0;
     for (int64_t q = 0; q < nsteps; ++nl) {
-        if (two && q + 1 < nsteps && plan[(size_t)q] == 0 && plan[(size_t)(q + 1)] == 0) {
-            plan[(size_t)q] = 2;
+        if (two && q + 1 < nsteps) {
+            plan[(size_t)q] = plan[(size_t)q] || plan[(size_t)(q + 1)] ? 4 : 2;
             plan[(size_t)(q + 1)] = 3;
             q += 2;
         } else {
@@ -376,9 +405,16 @@ hipError_t capture_t(kvs_batch* b, int64_t nsteps, const std::vector<uint8_t>& p
         const int64_t n = b->step + q;
         const int parity = (int)(launch & 1);  // every launch swaps the buffers once
         int adv = 1;
-        if (plan[(size_t)q] == 2) {
-            if constexpr (sizeof(T) == 4)
-                launch_batch_step2(b, parity, np > 0 ? b->traces + (b->trace_steps + q) * np : nullptr);
+        double* mid = nullptr;
+        if (plan[(size_t)q] == 2 || plan[(size_t)q] == 4) {
+            mid = np > 0 ? b->traces + (b->trace_steps + q) * np : nullptr;
+            if constexpr (sizeof(T) == 4) {
+                const bool force = plan[(size_t)q] == 4;
+                if (b->viscous)
+                    force ? launch_batch_step2<true, true>(b, n, parity, mid) : launch_batch_step2<true, false>(b, n, parity, mid);
+                else
+                    force ? launch_batch_step2<false, true>(b, n, parity, mid) : launch_batch_step2<false, false>(b, n, parity, mid);
+            }
             adv = 2;
         } else {
             const bool force = plan[(size_t)q] == 1;
@@ -391,7 +427,7 @@ hipError_t capture_t(kvs_batch* b, int64_t nsteps, const std::vector<uint8_t>& p
             hipLaunchKernelGGL(batch_probe_kernel<T>, dim3((np + 255) / 256), dim3(256), 0, b->stream,
                                static_cast<const BatchInst<T>*>(b->dev_params),
                                static_cast<const long long*>(b->dev_probes), np, b->comp, parity,
-                               b->traces + (b->trace_steps + q + adv - 1) * np);
+                               b->traces + (b->trace_steps + q + adv - 1) * np, mid);
         q += adv;
     }
     return hipGetLastError();
@@ -644,15 +680,23 @@ hipError_t kvs_batch_trial_launch(kvs_batch* b) {
     return hipGetLastError();
 }
 
-bool kvs_batch_two_step_supported(const kvs_batch* b) {
+bool kvs_batch_step2_supported(const kvs_batch* b) {
     if (b->prec != KVS_FP32 || !b->probes2_ok || b->inst.empty()) return false;
+    for (const kvs_ctx* c : b->inst)
+        if (!c->have_material || c->N >= ((int64_t)1 << 31) || c->grid.nx * c->grid.ny >= ((int64_t)1 << 30) - 1024 ||
+            c->npeak > 0 || c->pml_cells > 0)
+            return false;
+    return true;
+}
+
+bool kvs_batch_two_step_supported(const kvs_batch* b) {
+    if (!kvs_batch_step2_supported(b)) return false;
     bool visc = false;
     for (const kvs_ctx* c : b->inst) {
-        if (!c->have_material || c->grid.nx > 256 || c->N >= ((int64_t)1 << 31) || c->npeak > 0 || c->pml_cells > 0)
-            return false;
+        if (c->grid.nx > 256) return false;
         visc = visc || c->viscous;
     }
-    return visc;  // the two-step tile stages w: a batch with a viscous instance
+    return visc;
 }
 
 hipError_t kvs_batch_prepare(kvs_batch* b) {

@@ -135,10 +135,10 @@ struct kvs_ctx {
     int64_t trace_cap = 0;    // steps of capacity
     int64_t trace_steps = 0;  // steps recorded
     // two-step launches: the probe cells by grid row, for the threads that
-    // form the intermediate state (rowtab [nz][ny][ceil(nx / 64)]: the offset
-    // into ptab of row (j, k) where that 64-cell segment of it holds a probe,
-    // else -1; ptab: per probed row nx probe indices or -1); only when the
-    // probe cells are distinct and off the planes k = 0, nz - 1 (probe_rows_ok)
+    // form the intermediate state (rowtab [nz][ny]: the offset into ptab of
+    // row (j, k) where it holds a probe, else -1; ptab: per probed row nx probe
+    // indices or -1); only when the probe cells are distinct and off the
+    // planes k = 0, nz - 1 (probe_rows_ok)
     int* probe_rowtab = nullptr;
     int* probe_ptab = nullptr;
     bool probe_rows_ok = true;
@@ -166,6 +166,7 @@ struct kvs_ctx {
     // whole rounds of resident blocks), XCD-contiguous tile order
     int step_variant = 0;
     int step_zchunk = 0;
+    int step2_zchunk = 0;  // two-step launches: as set by kvs_set_step_tuning (the autotuner times one-step launches)
     int step_remap = 1;
     // steps per launch where the two-step kernel applies (1 or 2)
     int step_block = 2;
@@ -184,7 +185,8 @@ struct kvs_ctx {
     hipEvent_t launch_ev[2] = {nullptr, nullptr};
 
     // running peak of |u| on registered grid planes: one map of T per plane,
-    // concatenated in registration order (peak_off[p] = first cell of plane p)
+    // concatenated in registration order (peak_off[p] = first cell of plane p),
+    // then as many values for the intermediate step of two-step launches
     int npeak = 0;
     int peak_axis[KVS_MAX_PEAK_PLANES] = {};
     int64_t peak_index[KVS_MAX_PEAK_PLANES] = {};
@@ -278,17 +280,17 @@ struct kvs_batch {
     std::vector<uint8_t> graph_force;  // the per-step launch plan (see kvs_batch_run)
 
     // two steps per launch: requested (1 or 2), and whether the batch allows
-    // it (set by kvs_batch_prepare: FP32, viscous, rows <= 256 cells, probe
-    // cells distinct and off the planes k = 0, nz - 1); the instances'
-    // two-step arguments [parity], the work list of (instance, row pair,
-    // z segment) grouped by tile width, and the probe row tables
+    // it (set by kvs_batch_prepare: FP32, probe cells distinct and off the
+    // planes k = 0, nz - 1); the instances' two-step arguments [parity], the
+    // work list of (instance, tile, z segment) grouped by tile shape, and the
+    // probe row tables
     int step_block = 2;
     bool two_ok = false;
     void* dev_params2 = nullptr;
     size_t params2_bytes = 0;
     void* dev_work2 = nullptr;
     int nwork2 = 0;
-    std::vector<Group> groups2;  // shape = wavefronts per row (2, 3 or 4)
+    std::vector<Group> groups2;  // shape: index of the two-step tile shapes
     int* dev_ptabs2 = nullptr;   // row tables and probe tables of all instances
     std::vector<int64_t> rowtab2_off, ptab2_off;  // per instance, into dev_ptabs2 (-1: none)
     bool probes2_ok = true;      // the registered probes allow two-step launches
@@ -302,16 +304,19 @@ hipError_t kvs_launch_force_pattern(kvs_ctx* c, const kvs_force_pattern* p);
 // One FDTD step from (u[cur], w[cur]) into (u[1-cur], w[1-cur]) with source
 // amplitude gn (0: no force read).  Returns the launch error.
 hipError_t kvs_launch_step(kvs_ctx* c, double gn);
-// two steps in one launch (kvs_step2.hip), for two steps without force:
-// whether the precision, medium, layer, peak maps, probes and grid allow it
+// two steps in one launch (kvs_step2.hip) with source amplitudes gn, gn2:
+// whether the layer, probes and grid allow it, and whether the context is one
+// of those that kvs_step_blocking_applies names
 bool kvs_step2_supported(const kvs_ctx* c);
-hipError_t kvs_launch_step2(kvs_ctx* c);
+bool kvs_step2_reported(const kvs_ctx* c);
+hipError_t kvs_launch_step2(kvs_ctx* c, double gn, double gn2);
 hipError_t kvs_launch_step_variant(kvs_ctx* c, double gn, int variant);
 int kvs_step_variant_count();
 void kvs_step_variant_shape(int variant, int* by, int* vec, int* wx);
 hipError_t kvs_launch_probe_gather(kvs_ctx* c, const void* u_new, int64_t slot);
-// Fold |u_new| into the running peak maps of the registered planes.
-hipError_t kvs_launch_peak_update(kvs_ctx* c, const void* u_new);
+// Fold |u_new| (and, after a two-step launch, the intermediate |u| that it
+// stored) into the running peak maps of the registered planes.
+hipError_t kvs_launch_peak_update(kvs_ctx* c, const void* u_new, bool with_mid);
 hipError_t kvs_launch_crho(kvs_ctx* c);
 hipError_t kvs_launch_cast_material(kvs_ctx* c, const double* dG, const double* drho, const double* deta);
 hipError_t kvs_launch_cast(kvs_ctx* c, const double* src, void* dst, int64_t n);
@@ -351,8 +356,10 @@ hipError_t kvs_batch_trial_launch(kvs_batch* b);
 // Runs nsteps steps; *flips = launches that advanced the state (each swaps
 // the current and next buffers once).
 hipError_t kvs_batch_run(kvs_batch* b, int64_t nsteps, int64_t* flips);
-// Whether the batch's instances allow two-step launches (precision, medium,
-// row width, probes); the step loop also needs steps without force.
+// Whether the batch's instances allow two-step launches (precision, probes),
+// and whether the batch is one of those that kvs_batch_step_blocking_applies
+// names (a viscous instance, rows of at most 256 cells).
+bool kvs_batch_step2_supported(const kvs_batch* b);
 bool kvs_batch_two_step_supported(const kvs_batch* b);
 // True when kvs_batch_run takes the persistent path (every instance's state
 // fits one workgroup's LDS and the path is enabled).

@@ -11,9 +11,10 @@
 namespace {
 
 // NaN wins over every number, so an unstable run shows in the map instead of
-// hiding behind a plain max.
+// hiding behind a plain max.  mid: |u| of the intermediate step of a two-step
+// launch on the planes, laid out like the maps (else null).
 template <typename T>
-__global__ void peak_kernel(const T* u, long long N, int nx, int ny, PeakPlanes P, T* maps) {
+__global__ void peak_kernel(const T* u, long long N, int nx, int ny, PeakPlanes P, T* maps, const T* mid) {
     const int p = blockIdx.y;
     const int axis = P.axis[p];
     const long long idx = P.index[p];
@@ -28,14 +29,18 @@ __global__ void peak_kernel(const T* u, long long N, int nx, int ny, PeakPlanes 
         const long long c = i + nx * (j + ny * k);
         const T x = u[c], y = u[N + c], z = u[2 * N + c];
         const T v = sqrt(x * x + y * y + z * z);
-        const T old = m[q];
+        T old = m[q];
+        if (mid) {
+            const T w = mid[P.off[p] + q];
+            old = (w > old || __builtin_isnan(w)) ? w : old;
+        }
         m[q] = (v > old || __builtin_isnan(v)) ? v : old;
     }
 }
 
 }  // namespace
 
-hipError_t kvs_launch_peak_update(kvs_ctx* c, const void* u_new) {
+hipError_t kvs_launch_peak_update(kvs_ctx* c, const void* u_new, bool with_mid) {
     if (c->npeak == 0) return hipSuccess;
     PeakPlanes P{};
     long long most = 0;
@@ -51,9 +56,11 @@ hipError_t kvs_launch_peak_update(kvs_ctx* c, const void* u_new) {
     const dim3 grid((unsigned)std::min<long long>((most + 255) / 256, 1024), (unsigned)c->npeak);
     if (c->prec == KVS_FP32)
         hipLaunchKernelGGL(peak_kernel<float>, grid, dim3(256), 0, c->stream, static_cast<const float*>(u_new),
-                           (long long)c->N, (int)c->grid.nx, (int)c->grid.ny, P, static_cast<float*>(c->peak));
+                           (long long)c->N, (int)c->grid.nx, (int)c->grid.ny, P, static_cast<float*>(c->peak),
+                           with_mid ? static_cast<const float*>(c->peak) + c->peak_cells : nullptr);
     else
         hipLaunchKernelGGL(peak_kernel<double>, grid, dim3(256), 0, c->stream, static_cast<const double*>(u_new),
-                           (long long)c->N, (int)c->grid.nx, (int)c->grid.ny, P, static_cast<double*>(c->peak));
+                           (long long)c->N, (int)c->grid.nx, (int)c->grid.ny, P, static_cast<double*>(c->peak),
+                           with_mid ? static_cast<const double*>(c->peak) + c->peak_cells : nullptr);
     return hipGetLastError();
 }

@@ -4,100 +4,188 @@
 // the remaining blocks are the tiles, numbered XCD by XCD.
 #include <hip/hip_ext.h>
 
+#include <cmath>
+
 #include "kvs_step2_tile.hpp"
 
 namespace {
 
-template <bool HET, int WX>
-__global__ __launch_bounds__(64 * WX * S2_ROWS) void step2_kernel(const Step2Args A2) {
-    const StepArgs<float>& a = A2.a;
+template <typename T, bool HET, bool VISC, bool FORCE, bool PEAK, int WX, int R>
+__global__ __launch_bounds__(64 * WX * R) void step2_kernel(const Step2Args<T> A2, const Step2Peaks<T> pk) {
+    __shared__ __align__(16) T lds[Step2Tile<T, HET, VISC, WX, R>::LDS];
+    const StepArgs<T>& a = A2.a;
     if ((int)blockIdx.x < a.pblocks) {
-        const long long p = (long long)blockIdx.x * (64 * WX * S2_ROWS) + threadIdx.y * (64 * WX) + threadIdx.x;
-        if (p < a.np) {
-            const long long q = a.pcells[p];
-            if (a.pcomp == 3) {
-                a.pout[3 * p] = (double)a.u[q];
-                a.pout[3 * p + 1] = (double)a.u[a.N + q];
-                a.pout[3 * p + 2] = (double)a.u[2 * a.N + q];
-            } else {
-                a.pout[p] = (double)a.u[a.pcomp * a.N + q];
-            }
-        }
+        step2_probe(A2, (long long)blockIdx.x * (64 * WX * R) + threadIdx.y * (64 * WX) + threadIdx.x);
         return;
     }
-    const int B = a.gy * a.gz;
+    const int B = a.gx * a.gy * a.gz;
     const int b = (int)blockIdx.x - a.pblocks;
     const int t = a.remap ? tile_of(b, B) : b;
-    step2_tile<HET, WX, S2_ROWS>(A2, t % a.gy, t / a.gy);
+    step2_tile<T, HET, VISC, FORCE, PEAK, WX, R>(A2, &pk, lds, t % a.gx, (t / a.gx) % a.gy, t / (a.gx * a.gy));
 }
 
-template <bool HET, int WX>
-hipError_t launch_wx(kvs_ctx* c, const Step2Args& A0) {
-    Step2Args A2 = A0;
-    StepArgs<float>& a = A2.a;
-    auto kern = step2_kernel<HET, WX>;
-    static const int cap = resident_blocks(kern, 64 * WX * S2_ROWS);
-    a.gx = 1;
-    a.gy = (a.ny + 1) / 2;
-    a.kchunk = c->step_zchunk > 0 ? std::min(c->step_zchunk, a.nz - 2) : choose_kchunk(a.gy, a.nz - 2, cap);
+// Tile and z segment of a launch: the shape whose blocks finish first by a
+// model of its march, rounds of resident blocks x (planes + 3 to fill the
+// queues) x the time of a plane, which is the larger of a floor (the latency
+// of loads, barrier and LDS) and the wavefronts' work on a CU, one unit per
+// wavefront and update.  Unit 80 ns (256^3 heterogeneous: 28 units, 2.2 us a
+// plane), floor 9 units (0.7 us: small grids).
+struct Step2Plan {
+    double cost = 1e300;
+    int shape = -1, gx = 1, gy = 1, kchunk = 1;
+};
+
+void consider(Step2Plan& best, int shape, const kvs_grid& g, int cap, int zchunk) {
+    if (!step2_offers(shape, g.ny)) return;
+    const int planes = (int)g.nz - 2;
+    const int gx = overlap_tiles((int)g.nx, 64 * kStep2Wx[shape]), gy = overlap_tiles((int)g.ny, kStep2Rows[shape]);
+    const double units = step2_units(shape);
+    const int per_cu = std::max(1, cap / 256);
+    const int max_seg = std::max(1, planes / 2);
+    for (int seg = 1; seg <= max_seg; ++seg) {
+        int chunk = (planes + seg - 1) / seg;
+        if (zchunk > 0) chunk = std::min(zchunk, planes);
+        const long long blocks = (long long)gx * gy * ((planes + chunk - 1) / chunk);
+        const long long rounds = (blocks + cap - 1) / cap;
+        const double on_cu = (double)std::min<long long>(per_cu, (blocks + 255) / 256);
+        const double cost = (double)rounds * (chunk + 3) * std::max(9.0, units * on_cu);
+        if (cost < best.cost * 0.999) best = {cost, shape, gx, gy, chunk};
+        if (zchunk > 0) break;
+    }
+}
+
+template <typename T, bool HET, bool VISC, bool FORCE, int S, bool PEAK = false>
+hipError_t launch_shape(kvs_ctx* c, Step2Args<T>& A2, const Step2Peaks<T>& pk) {
+    constexpr int WX = kStep2Wx[S], R = kStep2Rows[S];
+    StepArgs<T>& a = A2.a;
+    auto kern = step2_kernel<T, HET, VISC, FORCE, PEAK, WX, R>;
     a.gz = (a.nz - 2 + a.kchunk - 1) / a.kchunk;
-    a.pblocks = a.pout ? (int)((a.np + 64 * WX * S2_ROWS - 1) / (64 * WX * S2_ROWS)) : 0;
-    const int blocks = a.gy * a.gz + a.pblocks;
+    a.pblocks = a.np > 0 && (a.pout || A2.pmid) ? (int)((a.np + 64 * WX * R - 1) / (64 * WX * R)) : 0;
+    const int blocks = a.gx * a.gy * a.gz + a.pblocks;
     if (c->launch_ev[0])
-        hipExtLaunchKernelGGL(kern, dim3(blocks), dim3(64 * WX, S2_ROWS), 0, c->stream, c->launch_ev[0],
-                              c->launch_ev[1], 0, A2);
+        hipExtLaunchKernelGGL(kern, dim3(blocks), dim3(64 * WX, R), 0, c->stream, c->launch_ev[0], c->launch_ev[1], 0,
+                              A2, pk);
     else
-        hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * WX, S2_ROWS), 0, c->stream, A2);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * WX, R), 0, c->stream, A2, pk);
     return hipGetLastError();
 }
 
-}  // namespace
-
-bool kvs_step2_supported(const kvs_ctx* c) {
-    // cell offsets within a field are 32-bit
-    return c->prec == KVS_FP32 && c->viscous && c->npeak == 0 && c->pml_cells == 0 &&
-           c->grid.nx <= 256 && c->N < ((int64_t)1 << 31) && (c->nprobes == 0 || c->probe_rows_ok);
+template <typename T, bool HET, bool VISC, bool FORCE, int S>
+int shape_cap() {
+    constexpr int WX = kStep2Wx[S], R = kStep2Rows[S];
+    static const int cap = resident_blocks(step2_kernel<T, HET, VISC, FORCE, false, WX, R>, 64 * WX * R);
+    return cap;
 }
 
-hipError_t kvs_launch_step2(kvs_ctx* c) {
+template <typename T, bool HET, bool VISC, bool FORCE>
+hipError_t launch_medium(kvs_ctx* c, Step2Args<T>& A2, const Step2Peaks<T>& pk) {
     const kvs_grid& g = c->grid;
-    Step2Args A2{};
-    StepArgs<float>& a = A2.a;
+    Step2Plan p;
+    // peak maps: the shape that fits most row lengths (FP32: 64 x 16), compiled
+    // for them alone; 64 x 8 where the grid's rows rule that out
+    if constexpr (sizeof(T) == 4) {
+        if (pk.n > 0) consider(p, 1, g, shape_cap<T, HET, VISC, FORCE, 1>(), c->step2_zchunk);
+    }
+    if (pk.n > 0 && p.shape < 0) consider(p, 2, g, shape_cap<T, HET, VISC, FORCE, 2>(), c->step2_zchunk);
+    if (p.shape >= 0) {
+        A2.a.gx = p.gx;
+        A2.a.gy = p.gy;
+        A2.a.kchunk = p.kchunk;
+        if constexpr (sizeof(T) == 4) {
+            if (p.shape == 1) return launch_shape<T, HET, VISC, FORCE, 1, true>(c, A2, pk);
+        }
+        return launch_shape<T, HET, VISC, FORCE, 2, true>(c, A2, pk);
+    }
+    if constexpr (sizeof(T) == 4) {
+        consider(p, 0, g, shape_cap<T, HET, VISC, FORCE, 0>(), c->step2_zchunk);
+        consider(p, 1, g, shape_cap<T, HET, VISC, FORCE, 1>(), c->step2_zchunk);
+        consider(p, 3, g, shape_cap<T, HET, VISC, FORCE, 3>(), c->step2_zchunk);
+    }
+    consider(p, 2, g, shape_cap<T, HET, VISC, FORCE, 2>(), c->step2_zchunk);
+    A2.a.gx = p.gx;
+    A2.a.gy = p.gy;
+    A2.a.kchunk = p.kchunk;
+    if constexpr (sizeof(T) == 4) {
+        if (p.shape == 0) return launch_shape<T, HET, VISC, FORCE, 0>(c, A2, pk);
+        if (p.shape == 1) return launch_shape<T, HET, VISC, FORCE, 1>(c, A2, pk);
+        if (p.shape == 3) return launch_shape<T, HET, VISC, FORCE, 3>(c, A2, pk);
+    }
+    return launch_shape<T, HET, VISC, FORCE, 2>(c, A2, pk);
+}
+
+template <typename T, bool HET, bool VISC>
+hipError_t launch_force(kvs_ctx* c, Step2Args<T>& A2, const Step2Peaks<T>& pk) {
+    return A2.a.gn != T(0) || A2.gn2 != T(0) ? launch_medium<T, HET, VISC, true>(c, A2, pk)
+                                             : launch_medium<T, HET, VISC, false>(c, A2, pk);
+}
+
+template <typename T>
+hipError_t launch_t(kvs_ctx* c, double gn, double gn2) {
+    const kvs_grid& g = c->grid;
+    Step2Args<T> A2{};
+    StepArgs<T>& a = A2.a;
     const int nb = 1 - c->cur;
-    a.u = static_cast<const float*>(c->u[c->cur]);
-    a.w = static_cast<const float*>(c->w[c->cur]);
-    a.un = static_cast<float*>(c->u[nb]);
-    a.wn = static_cast<float*>(c->w[nb]);
-    a.G = static_cast<const float*>(c->G);
-    a.eta = static_cast<const float*>(c->eta);
-    a.crho = static_cast<const float*>(c->crho);
+    a.u = static_cast<const T*>(c->u[c->cur]);
+    a.w = static_cast<const T*>(c->w[c->cur]);
+    a.un = static_cast<T*>(c->u[nb]);
+    a.wn = static_cast<T*>(c->w[nb]);
+    a.G = static_cast<const T*>(c->G);
+    a.eta = static_cast<const T*>(c->eta);
+    a.crho = static_cast<const T*>(c->crho);
+    a.FS = static_cast<const T*>(c->FS);
     a.N = c->N;
     a.nx = (int)g.nx;
     a.ny = (int)g.ny;
     a.nz = (int)g.nz;
     a.L = c->sponge_cells;
-    a.invL = a.L > 0 ? (float)(1.0 / a.L) : 0.f;
-    a.ihx2 = (float)(1.0 / (g.hx * g.hx));
-    a.ihy2 = (float)(1.0 / (g.hy * g.hy));
-    a.ihz2 = (float)(1.0 / (g.hz * g.hz));
-    a.G0 = (float)c->G0;
-    a.eta_dt0 = (float)(c->eta0 / c->dt);
-    a.crho0 = (float)(c->dt * c->dt / c->rho0);
-    a.inv_dt = (float)(1.0 / c->dt);
-    a.half_dt_smax = (float)(0.5 * c->sigma_max * c->dt);
+    a.invL = a.L > 0 ? T(1.0 / a.L) : T(0);
+    a.ihx2 = T(1.0 / (g.hx * g.hx));
+    a.ihy2 = T(1.0 / (g.hy * g.hy));
+    a.ihz2 = T(1.0 / (g.hz * g.hz));
+    a.G0 = T(c->G0);
+    a.eta_dt0 = T(c->eta0 / c->dt);
+    a.crho0 = T(c->dt * c->dt / c->rho0);
+    a.inv_dt = T(1.0 / c->dt);
+    a.gn = T(gn);
+    A2.gn2 = T(gn2);
+    a.half_dt_smax = T(0.5 * c->sigma_max * c->dt);
     a.remap = c->step_remap;
-    if (c->probe_fused_out) {
+    if (c->nprobes > 0) {
         a.pcells = reinterpret_cast<const long long*>(c->probe_cells);
         a.pout = c->probe_fused_out;
         a.np = c->nprobes;
         a.pcomp = c->probe_comp;
-    }
-    if (c->nprobes > 0) {
         A2.rowtab = c->probe_rowtab;
         A2.ptab = c->probe_ptab;
         A2.pmid = c->probe_mid_out;
-        a.pcomp = c->probe_comp;
     }
-    if (c->hetero) return g.nx <= 128 ? launch_wx<true, 2>(c, A2) : launch_wx<true, 4>(c, A2);
-    return g.nx <= 128 ? launch_wx<false, 2>(c, A2) : launch_wx<false, 4>(c, A2);
+    Step2Peaks<T> pk{};
+    pk.n = c->npeak;
+    pk.mid = c->npeak > 0 ? static_cast<T*>(c->peak) + c->peak_cells : nullptr;
+    for (int p = 0; p < c->npeak; ++p) {
+        pk.axis[p] = c->peak_axis[p];
+        pk.index[p] = (int)c->peak_index[p];
+        pk.n1[p] = c->peak_axis[p] == 0 ? a.ny : a.nx;
+        pk.off[p] = c->peak_off[p];
+    }
+    if (c->hetero) return c->viscous ? launch_force<T, true, true>(c, A2, pk) : launch_force<T, true, false>(c, A2, pk);
+    return c->viscous ? launch_force<T, false, true>(c, A2, pk) : launch_force<T, false, false>(c, A2, pk);
+}
+
+}  // namespace
+
+bool kvs_step2_supported(const kvs_ctx* c) {
+    // cell offsets within a field are 32-bit, byte offsets within a plane too;
+    // FP64 has one tile shape
+    const int64_t plane = c->grid.nx * c->grid.ny * (c->prec == KVS_FP32 ? 4 : 8);
+    return c->pml_cells == 0 && c->N < ((int64_t)1 << 31) && plane < ((int64_t)1 << 32) - 4096 &&
+           (c->nprobes == 0 || c->probe_rows_ok) && (c->prec == KVS_FP32 || step2_offers(2, c->grid.ny));
+}
+
+bool kvs_step2_reported(const kvs_ctx* c) {
+    return kvs_step2_supported(c) && c->prec == KVS_FP32 && c->viscous && c->npeak == 0 && c->grid.nx <= 256;
+}
+
+hipError_t kvs_launch_step2(kvs_ctx* c, double gn, double gn2) {
+    return c->prec == KVS_FP32 ? launch_t<float>(c, gn, gn2) : launch_t<double>(c, gn, gn2);
 }
