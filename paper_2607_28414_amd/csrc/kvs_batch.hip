@@ -2,6 +2,9 @@
 // launch per step over every instance's tiles (captured once as a hipGraph
 // and replayed), or, when every instance's state fits one workgroup's LDS,
 // one persistent launch for the whole run.
+#include <algorithm>
+#include <functional>
+
 #include "kvs_step2_tile.hpp"
 #include "kvs_step_tile.hpp"
 
@@ -254,16 +257,69 @@ struct BatchInst2 {
     long long probe0;  // the instance's first probe in the flat probe list
 };
 
-constexpr int kStep2Zchunk = 64;  // z planes per block of the two-step launches
+// An instance's z segments: equal ones of at most `most` planes.
+inline int step2_chunk(int64_t nz, int most) {
+    const int planes = (int)nz - 2, seg = (planes + most - 1) / most;
+    return (planes + seg - 1) / seg;
+}
+
+// A group's work list and its launch order.  Block b runs on XCD b mod 8, so
+// the list is cut into eight runs of neighbouring tiles with equal work (planes
+// to march and 3 to fill the queues), one per XCD, each issued longest block
+// first; entries -1 fill the shorter runs.  span: when the last block ends if
+// every CU marches one block at a time.
+struct Step2List {
+    std::vector<int4> order;
+    long long span = 0;
+};
+Step2List step2_list(const kvs_batch* b, const std::vector<int>& members, int shape, int most) {
+    std::vector<int4> work;
+    std::vector<int> planes;
+    long long total = 0, sum = 0;
+    for (int i : members) {
+        const kvs_grid& g = b->inst[(size_t)i]->grid;
+        const int gx = overlap_tiles((int)g.nx, 64 * kStep2Wx[shape]), gy = overlap_tiles((int)g.ny, kStep2Rows[shape]);
+        const int chunk = step2_chunk(g.nz, most), np = (int)g.nz - 2;
+        for (int bz = 0; bz * chunk < np; ++bz)
+            for (int by = 0; by < gy; ++by)
+                for (int bx = 0; bx < gx; ++bx) {
+                    work.push_back(make_int4(i, bx, by, bz));
+                    planes.push_back(std::min(chunk, np - bz * chunk) + 3);
+                    total += planes.back();
+                }
+    }
+    std::vector<std::vector<int>> run(8);
+    size_t longest = 0;
+    for (size_t q = 0; q < work.size(); ++q) {
+        run[(size_t)std::min<long long>(7, 8 * sum / std::max(1LL, total))].push_back((int)q);
+        sum += planes[q];
+    }
+    Step2List out;
+    for (auto& r : run) {
+        std::stable_sort(r.begin(), r.end(), [&](int x, int y) { return planes[(size_t)x] > planes[(size_t)y]; });
+        longest = std::max(longest, r.size());
+        std::vector<long long> cu(32, 0);  // min-heap: when each CU of the XCD is free
+        for (int q : r) {
+            std::pop_heap(cu.begin(), cu.end(), std::greater<long long>());
+            cu.back() += planes[(size_t)q];
+            out.span = std::max(out.span, cu.back());
+            std::push_heap(cu.begin(), cu.end(), std::greater<long long>());
+        }
+    }
+    out.order.assign(8 * longest, make_int4(-1, 0, 0, 0));
+    for (size_t x = 0; x < 8; ++x)
+        for (size_t q = 0; q < run[x].size(); ++q) out.order[8 * q + x] = work[(size_t)run[x][q]];
+    return out;
+}
 
 // FORCE: some instance's envelope is non-zero in one of the two steps; the
 // others take the tile without force.
 template <bool VISC, bool FORCE, int WX, int R>
-__global__ __launch_bounds__(64 * WX * R) void batch_step2_kernel(const BatchInst2* inst, const int4* work, int nwork,
-                                                                  long long n, int parity, double* slot) {
+__global__ __launch_bounds__(64 * WX * R) void batch_step2_kernel(const BatchInst2* inst, const int4* work, long long n,
+                                                                  int parity, double* slot) {
     __shared__ __align__(16) float lds[Step2Tile<float, false, VISC, WX, R>::LDS];
-    const int t = tile_of(blockIdx.x, nwork);
-    const int4 wi = work[t];
+    const int4 wi = work[blockIdx.x];
+    if (wi.x < 0) return;  // an XCD's list shorter than the longest
     const BatchInst2& bi = inst[wi.x];
     Step2Args<float> A = bi.a2[parity];
     A.pmid = slot != nullptr && A.rowtab != nullptr ? slot + bi.probe0 : nullptr;
@@ -300,6 +356,33 @@ hipError_t prepare2(kvs_batch* b) {
     b->two_ok = kvs_batch_step2_supported(b);
     if (!b->two_ok) return hipSuccess;
     const int n = (int)b->inst.size();
+    std::vector<int4> work;
+    if (!b->dev_work2) {
+        // per tile shape the segment length whose launch ends first.  Measured,
+        // us per step, 24 instances of edges 64 to 160: segments of 64 planes in
+        // XCD-contiguous order 375, 32 planes in this order 320; 64 instances
+        // of edges 96 to 192: 1521, and 1455 with 96 planes
+        b->groups2.clear();
+        b->chunk2.assign((size_t)n, 1);
+        for (int sh = 0; sh < kStep2Shapes; ++sh) {
+            std::vector<int> members;
+            for (int i = 0; i < n; ++i)
+                if (step2_shape(b->inst[(size_t)i]->grid) == sh) members.push_back(i);
+            if (members.empty()) continue;
+            Step2List best;
+            int most = 0;
+            for (int m : {8, 12, 16, 24, 32, 48, 64, 96, 128}) {
+                Step2List l = step2_list(b, members, sh, m);
+                if (most == 0 || l.span < best.span) {
+                    best = std::move(l);
+                    most = m;
+                }
+            }
+            for (int i : members) b->chunk2[(size_t)i] = step2_chunk(b->inst[(size_t)i]->grid.nz, most);
+            b->groups2.push_back({sh, (int)work.size(), (int)best.order.size()});
+            work.insert(work.end(), best.order.begin(), best.order.end());
+        }
+    }
     std::vector<BatchInst2> params((size_t)n);
     const double* env = reinterpret_cast<const double*>(static_cast<const char*>(b->dev_params) +
                                                         sizeof(BatchInst<float>) * (size_t)n);
@@ -307,13 +390,10 @@ hipError_t prepare2(kvs_batch* b) {
         kvs_ctx* c = b->inst[(size_t)i];
         const int64_t roff = i < (int)b->rowtab2_off.size() ? b->rowtab2_off[(size_t)i] : -1;
         const int64_t poff = i < (int)b->ptab2_off.size() ? b->ptab2_off[(size_t)i] : -1;
-        const int sh = step2_shape(c->grid);
         for (int par = 0; par < 2; ++par) {
             Step2Args<float>& A = params[(size_t)i].a2[par];
             A = Step2Args<float>{};
-            A.a = instance_args<float>(c, par == 0 ? c->cur : 1 - c->cur, 4, 1, 1, kStep2Zchunk);
-            A.a.gx = overlap_tiles(A.a.nx, 64 * kStep2Wx[sh]);
-            A.a.gy = overlap_tiles(A.a.ny, kStep2Rows[sh]);
+            A.a = instance_args<float>(c, par == 0 ? c->cur : 1 - c->cur, 4, 1, 1, b->chunk2[(size_t)i]);
             A.a.pcomp = b->comp;
             A.rowtab = roff >= 0 ? b->dev_ptabs2 + roff : nullptr;
             A.ptab = poff >= 0 ? b->dev_ptabs2 + poff : nullptr;
@@ -335,19 +415,6 @@ hipError_t prepare2(kvs_batch* b) {
     }
     e = hipMemcpyAsync(b->dev_params2, params.data(), bytes, hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess && !b->dev_work2) {
-        std::vector<int4> work;
-        b->groups2.clear();
-        for (int sh = 0; sh < kStep2Shapes; ++sh) {
-            const int first = (int)work.size();
-            for (int i = 0; i < n; ++i) {
-                if (step2_shape(b->inst[(size_t)i]->grid) != sh) continue;
-                const StepArgs<float>& a = params[(size_t)i].a2[0].a;
-                for (int bz = 0; bz < a.gz; ++bz)
-                    for (int by = 0; by < a.gy; ++by)
-                        for (int bx = 0; bx < a.gx; ++bx) work.push_back(make_int4(i, bx, by, bz));
-            }
-            if ((int)work.size() > first) b->groups2.push_back({sh, first, (int)work.size() - first});
-        }
         e = b->mem.get(&b->dev_work2, sizeof(int4) * work.size());
         if (e == hipSuccess)
             e = hipMemcpyAsync(b->dev_work2, work.data(), sizeof(int4) * work.size(), hipMemcpyHostToDevice,
@@ -362,7 +429,7 @@ template <bool VISC, bool FORCE, int S>
 void launch_batch_step2_shape(kvs_batch* b, const kvs_batch::Group& g, long long n, int parity, double* slot) {
     hipLaunchKernelGGL((batch_step2_kernel<VISC, FORCE, kStep2Wx[S], kStep2Rows[S]>), dim3(g.count),
                        dim3(64 * kStep2Wx[S], kStep2Rows[S]), 0, b->stream, static_cast<const BatchInst2*>(b->dev_params2),
-                       static_cast<const int4*>(b->dev_work2) + g.off, g.count, n, parity, slot);
+                       static_cast<const int4*>(b->dev_work2) + g.off, n, parity, slot);
 }
 
 template <bool VISC, bool FORCE>

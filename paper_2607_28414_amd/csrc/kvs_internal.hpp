@@ -290,6 +290,7 @@ struct kvs_batch {
     size_t params2_bytes = 0;
     void* dev_work2 = nullptr;
     int nwork2 = 0;
+    std::vector<int> chunk2;  // z planes per block of each instance, as the work list has them
     std::vector<Group> groups2;  // shape: index of the two-step tile shapes
     int* dev_ptabs2 = nullptr;   // row tables and probe tables of all instances
     std::vector<int64_t> rowtab2_off, ptab2_off;  // per instance, into dev_ptabs2 (-1: none)
