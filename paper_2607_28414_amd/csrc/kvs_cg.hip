@@ -690,8 +690,7 @@ kvs_status cg_project(const CgBuffers& B, const kvs_solve_opts* o, kvs_solve_rep
         static const int cap2 = kvs_tiling::resident_blocks(cg_dir_kernel<2, 8, double, double>, 1024);
         static const int cap4 = kvs_tiling::resident_blocks(cg_dir_kernel<4, 4, double, double>, 1024);
         const int cap = shp.wx == 4 ? cap4 : (shp.wx == 2 ? cap2 : cap1);
-        sg.kchunk = kvs_tiling::choose_kchunk(sg.gx * sg.gy, g.nz - 2, cap,
-                                              kvs_tiling::cg_min_planes(sg.gx * sg.gy, g.nz - 2));
+        sg.kchunk = kvs_tiling::cg_kchunk(sg.gx * sg.gy, g.nz - 2, cap);
         sg.gz = (g.nz - 2 + sg.kchunk - 1) / sg.kchunk;
     }
     const int nbs = sg.gx * sg.gy * sg.gz;
@@ -761,7 +760,6 @@ kvs_status cg_project(const CgBuffers& B, const kvs_solve_opts* o, kvs_solve_rep
     int pi = 0;  // p[pi] holds the current search direction
     const long long cap = (o->fixed_iters > 0 ? o->fixed_iters : o->max_iter) + 1;
     double* z = B.Ap;  // flexible PCG: the preconditioned residual
-    const int* stop = &B.cgs->done;
     // flexible PCG keeps the previous residual for beta: the update writes
     // the new residual into the other buffer (rb[ri] is the current one)
     // FP32 direction and residual without a network: two iterations per pair

@@ -299,7 +299,7 @@ void kvs_cg_pair_launch(const kvs_grid& gr, const CgPair& c) {
     g.gx = overlap_tiles(g.nx, 64 * s.wx);
     g.gy = overlap_tiles(g.ny, s.rows);
     const int cap = s.rows == 16 ? pair_cap<1, 16>() : s.wx == 2 ? pair_cap<2, 8>() : pair_cap<1, 8>();
-    g.kchunk = kvs_tiling::choose_kchunk(g.gx * g.gy, g.nz - 2, cap, kvs_tiling::cg_min_planes(g.gx * g.gy, g.nz - 2));
+    g.kchunk = kvs_tiling::cg_kchunk(g.gx * g.gy, g.nz - 2, cap);
     g.gz = (g.nz - 2 + g.kchunk - 1) / g.kchunk;
     const int blocks = g.gx * g.gy * g.gz;
     if (s.rows == 16)

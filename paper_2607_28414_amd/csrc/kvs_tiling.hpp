@@ -54,12 +54,11 @@ __device__ __forceinline__ bool overlap_owns(int l, int t, int T, int i, int n) 
 }
 
 // Split z into segments so that (xy tiles) x (segments) fills whole rounds of
-// resident blocks; fewer, longer segments re-read fewer halo planes.  At
-// least min_planes planes per segment.
-inline int choose_kchunk(int xytiles, int planes, int cap, int min_planes = 8) {
+// resident blocks; fewer, longer segments re-read fewer halo planes.
+inline int choose_kchunk(int xytiles, int planes, int cap) {
     int best_seg = 1;
     double best = -1.0;
-    const int max_seg = std::max(1, planes / min_planes);
+    const int max_seg = std::max(1, planes / 8);
     for (int seg = 1; seg <= max_seg; ++seg) {
         const int chunk = (planes + seg - 1) / seg;
         const int nseg = (planes + chunk - 1) / chunk;
@@ -80,6 +79,32 @@ inline int choose_kchunk(int xytiles, int planes, int cap, int min_planes = 8) {
 // chip short of blocks, a sweep's time is its blocks' serial march, not their
 // halo planes, so segments of 2 planes are allowed.
 inline int cg_min_planes(int xytiles, int planes) { return (long long)xytiles * ((planes + 7) / 8) <= 1024 ? 2 : 8; }
+
+// z segment of a CG sweep.  Where short segments are allowed: the one with the
+// least rounds x (planes + 3 to start) x the time of a plane, which with one
+// block on a CU is the latency of its loads and barriers and grows by 0.8 of
+// that for each block more (us per iteration, FP32 pairs: 93 x 70 x 101 with
+// segments of 2, 4, 8 planes, 500, 250, 130 blocks: 17.0, 14.2, 17.0; 96^3 with
+// 3, 6, 12, 448, 224, 112 blocks: 18.7, 16.0, 20.3; 160 x 144 x 208 with 14, 24,
+// 495, 297 blocks: 39, 51).
+inline int cg_kchunk(int xytiles, int planes, int cap) {
+    if (cg_min_planes(xytiles, planes) == 8) return choose_kchunk(xytiles, planes, cap);
+    const int per_cu = std::max(1, cap / 256);
+    int best = planes;
+    double least = 1e300;
+    for (int seg = 1; seg <= std::max(1, planes / 2); ++seg) {
+        const int chunk = (planes + seg - 1) / seg;
+        const long long blocks = (long long)xytiles * ((planes + chunk - 1) / chunk);
+        const long long rounds = (blocks + cap - 1) / cap;
+        const double on_cu = (double)std::min<long long>(per_cu, (blocks + 255) / 256);
+        const double cost = (double)rounds * (chunk + 3) * std::max(1.0, 0.8 * on_cu);
+        if (cost < least * 0.999) {
+            least = cost;
+            best = chunk;
+        }
+    }
+    return best;
+}
 
 // Upper bound on the blocks a CG sweep over `planes` z planes uses.
 inline long long max_tiled_blocks(int xytiles, int planes) {
