@@ -1251,81 +1251,263 @@ __global__ void f32_to_bf16(const float* __restrict__ a, bf16* __restrict__ b, l
     if (q < n) b[q] = (bf16)a[q];
 }
 
-// Weight gradient of one conv: part[tap][blk][co * CI + ci] =
-//   sum over the block's voxels v of x(v + dil tap)[ci] * dy[v][co],
-// x(p) = A[p] as the forward read it (or, FIRST, the scaled FP64 input
-// rounded to BF16); dy in FP32.  64 voxels are staged in
-// LDS at a time; each thread owns a fixed set of (co, ci) pairs.
-template <int CI, int CO, bool FIRST>
-__global__ __launch_bounds__(256) void dw_partial(const bf16* __restrict__ A, const double* __restrict__ r,
-                                                  double in_scale, Dims d, int dil,
-                                                  const float* __restrict__ dy, float* __restrict__ part) {
-    constexpr int NP = CI * CO;
-    constexpr int PER = (NP + 255) / 256;
-    __shared__ float xs[64][CI];
-    __shared__ float ys[64][CO];
-    const int tap = blockIdx.y;
-    const int ox = dil * tap_dx(tap), oy = dil * tap_dy(tap), oz = dil * tap_dz(tap);
-    const long long N = d.n();
-    float acc[PER];
+// ---- weight gradients ----
+// dW[tap][co][ci] = sum_v x(v + dil tap)[ci] dy[v][co] is a product over the
+// voxels, x in BF16 as the forward pass read it (or rounded to BF16), dy and
+// the sums in FP32: FP32 matrix instructions (16 x 16 x 4), which round as
+// FP32 multiplies and adds do.  Lane (i, q) of a wavefront holds voxel q of the
+// four of a step, and channels MT i .. MT i + MT - 1 of x and NT i .. of dy, one
+// load each: register m is the row i of tile m.  A wavefront marches over whole
+// x rows; the eight of a block are summed through LDS and the blocks by
+// dw_reduce, both in a fixed order.
+//
+// Partial sums leave in the order of the accumulators: element
+// ((tap * MT + m) * NT + n) * 256 + 64 r + lane is row 4 (lane / 16) + r, column
+// lane % 16 of tile (m, n).
+typedef float dw_f4 __attribute__((ext_vector_type(4)));
+
+constexpr int kDwWaves = 8;
+
+// sum of the block's wavefronts for 256 E accumulators, then one store
+template <int E>
+__device__ __forceinline__ void dw_block_sum(dw_f4 (&acc)[E], float* red, float* __restrict__ out, int w, int lane) {
+    auto put = [&](int slot) {
 #pragma unroll
-    for (int q = 0; q < PER; ++q) acc[q] = 0.f;
-    for (long long base = (long long)blockIdx.x * 64; base < N; base += (long long)gridDim.x * 64) {
-        for (int idx = threadIdx.x; idx < 64 * CI; idx += 256) {
-            const int vox = idx / CI, c = idx % CI;
-            const long long v = base + vox;
-            float val = 0.f;
-            if (v < N) {
-                const int x = (int)(v % d.nx) + ox, y = (int)((v / d.nx) % d.ny) + oy,
-                          z = (int)(v / ((long long)d.nx * d.ny)) + oz;
-                if (x >= 0 && x < d.nx && y >= 0 && y < d.ny && z >= 0 && z < d.nz) {
-                    const long long p = x + (long long)d.nx * (y + (long long)d.ny * z);
-                    if constexpr (FIRST) {
-                        val = (float)bf16_via_f32(in_scale * r[p]);
-                    } else {
-                        val = (float)A[p * CI + c];
+        for (int t = 0; t < E; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[(slot * E + t) * 256 + 64 * r + lane] = acc[t][r];
+    };
+    if (w >= 4) put(w - 4);
+    __syncthreads();
+    if (w < 4) {
+#pragma unroll
+        for (int t = 0; t < E; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[t][r] += red[(w * E + t) * 256 + 64 * r + lane];
+        put(w);
+    }
+    __syncthreads();
+    for (int q = 64 * w + lane; q < E * 256; q += 64 * kDwWaves)
+        out[q] = (red[q] + red[E * 256 + q]) + (red[2 * E * 256 + q] + red[3 * E * 256 + q]);
+    __syncthreads();  // the next tap's sums take the same LDS
+}
+
+// The rows of wavefront w of the grid's x dimension
+__device__ __forceinline__ void dw_rows(Dims d, int w, int& r0, int& r1) {
+    const long long rows = (long long)d.ny * d.nz, nw = (long long)gridDim.x * kDwWaves;
+    const long long q = (long long)blockIdx.x * kDwWaves + w;
+    r0 = (int)(rows * q / nw);
+    r1 = (int)(rows * (q + 1) / nw);
+}
+
+template <int K>
+struct DwVec;
+template <>
+struct DwVec<1> {
+    typedef unsigned short b;
+    typedef float f;
+};
+template <>
+struct DwVec<2> {
+    typedef unsigned short b __attribute__((ext_vector_type(2)));
+    typedef float f __attribute__((ext_vector_type(2)));
+};
+template <>
+struct DwVec<4> {
+    typedef unsigned short b __attribute__((ext_vector_type(4)));
+    typedef float f __attribute__((ext_vector_type(4)));
+};
+template <int K, typename V>
+__device__ __forceinline__ auto dw_at(const V& v, int q) {
+    if constexpr (K == 1)
+        return v;
+    else
+        return v[q];
+}
+
+// CI, CO multiples of 16; taps TPW blockIdx.y ..  Four steps of four voxels are
+// loaded ahead of their products.
+template <int CI, int CO, int TPW>
+__global__ __launch_bounds__(64 * kDwWaves) void dw_mfma(const bf16* __restrict__ A, Dims d, int dil,
+                                                         const float* __restrict__ dy, float* __restrict__ part) {
+    constexpr int MT = CI / 16, NT = CO / 16, E = MT * NT, U = 4;
+    typedef typename DwVec<MT>::b AV;
+    typedef typename DwVec<NT>::f BV;
+    __shared__ float red[4 * E * 256];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = lane & 15, kq = lane >> 4;
+    dw_f4 acc[TPW][E];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[t][e] = dw_f4{0.f, 0.f, 0.f, 0.f};
+    int r0, r1;
+    dw_rows(d, w, r0, r1);
+    for (int row = r0; row < r1; ++row) {
+        const int y = row % d.ny, z = row / d.ny;
+        const float* yrow = dy + (long long)row * d.nx * CO + NT * i;
+        const bf16* arow[TPW];
+        bool rok[TPW];
+        int ox[TPW];
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+            const int tap = TPW * (int)blockIdx.y + t;
+            const int yy = y + dil * tap_dy(tap), zz = z + dil * tap_dz(tap);
+            ox[t] = dil * tap_dx(tap);
+            rok[t] = yy >= 0 && yy < d.ny && zz >= 0 && zz < d.nz;
+            arow[t] = A + (rok[t] ? (long long)(zz * d.ny + yy) * d.nx * CI : 0LL) + MT * i;
+        }
+        for (int x0 = 0; x0 < d.nx; x0 += 4 * U) {
+            BV bv[U];
+            AV av[U][TPW];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int x = x0 + 4 * u + kq, xc = std::min(x, d.nx - 1);
+                bv[u] = *reinterpret_cast<const BV*>(yrow + xc * CO);
+#pragma unroll
+                for (int t = 0; t < TPW; ++t)
+                    av[u][t] = *reinterpret_cast<const AV*>(arow[t] + std::min(std::max(x + ox[t], 0), d.nx - 1) * CI);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (x0 + 4 * u >= d.nx) break;
+                const int x = x0 + 4 * u + kq;
+                float b[NT];
+#pragma unroll
+                for (int n = 0; n < NT; ++n) b[n] = x < d.nx ? dw_at<NT>(bv[u], n) : 0.f;
+#pragma unroll
+                for (int t = 0; t < TPW; ++t) {
+                    const int xx = x + ox[t];
+                    const bool ok = rok[t] && x < d.nx && xx >= 0 && xx < d.nx;
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) {
+                        const float a = ok ? __uint_as_float((unsigned)dw_at<MT>(av[u][t], m) << 16) : 0.f;
+#pragma unroll
+                        for (int n = 0; n < NT; ++n)
+                            acc[t][m * NT + n] =
+                                __builtin_amdgcn_mfma_f32_16x16x4f32(a, b[n], acc[t][m * NT + n], 0, 0, 0);
                     }
                 }
             }
-            xs[vox][c] = val;
         }
-        for (int idx = threadIdx.x; idx < 64 * CO; idx += 256) {
-            const int vox = idx / CO, c = idx % CO;
-            const long long v = base + vox;
-            ys[vox][c] = v < N ? dy[v * CO + c] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int pidx = threadIdx.x + 256 * q;
-            if (pidx < NP) {
-                const int co = pidx / CI, ci = pidx % CI;
-                float a = acc[q];
-                for (int vox = 0; vox < 64; ++vox) a += xs[vox][ci] * ys[vox][co];
-                acc[q] = a;
-            }
-        }
-        __syncthreads();
     }
+    float* out = part + ((long long)blockIdx.y * gridDim.x + blockIdx.x) * TPW * E * 256;
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int pidx = threadIdx.x + 256 * q;
-        if (pidx < NP) part[((long long)tap * gridDim.x + blockIdx.x) * NP + pidx] = acc[q];
-    }
+    for (int t = 0; t < TPW; ++t) dw_block_sum<E>(acc[t], red, out + t * E * 256, w, lane);
 }
 
-// grad[co][tap * CI + ci] (+)= sum over blocks, fixed order
-__global__ void dw_reduce(const float* __restrict__ part, int nblk, int CI, int CO, float* __restrict__ grad,
-                          int accumulate) {
-    const int NP = CI * CO;
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 27LL * NP) return;
-    const int tap = (int)(t / NP), pidx = (int)(t % NP);
+// One channel on one side: the taps are the other dimension of the product, in
+// two tiles.  FIRST: rows are taps, x = in_scale r rounded to BF16, columns the
+// 16 channels of dy.  Otherwise rows are the 16 channels of A[p], columns the
+// taps of dy[p - tap].
+template <bool FIRST>
+__global__ __launch_bounds__(64 * kDwWaves) void dw_taps(const bf16* __restrict__ A, const double* __restrict__ r,
+                                                         double in_scale, Dims d, const float* __restrict__ dy,
+                                                         float* __restrict__ part) {
+    constexpr int U = 4;
+    __shared__ float red[4 * 2 * 256];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = lane & 15, kq = lane >> 4;
+    constexpr int sgn = FIRST ? 1 : -1;
+    int ox[2], oy[2], oz[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int tap = std::min(16 * t + i, 26);
+        ox[t] = sgn * tap_dx(tap);
+        oy[t] = sgn * tap_dy(tap);
+        oz[t] = sgn * tap_dz(tap);
+    }
+    dw_f4 acc[2] = {dw_f4{0.f, 0.f, 0.f, 0.f}, dw_f4{0.f, 0.f, 0.f, 0.f}};
+    int r0, r1;
+    dw_rows(d, w, r0, r1);
+    for (int row = r0; row < r1; ++row) {
+        const int y = row % d.ny, z = row / d.ny;
+        long long grow[2];
+        bool rok[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int yy = y + oy[t], zz = z + oz[t];
+            rok[t] = 16 * t + i < 27 && yy >= 0 && yy < d.ny && zz >= 0 && zz < d.nz;
+            grow[t] = rok[t] ? (long long)(zz * d.ny + yy) * d.nx : 0LL;
+        }
+        const long long crow = (long long)row * d.nx;
+        for (int x0 = 0; x0 < d.nx; x0 += 4 * U) {
+            float c[U], g[U][2];
+            double rv[U][2];
+            unsigned short cb[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int x = x0 + 4 * u + kq, xc = std::min(x, d.nx - 1);
+                if constexpr (FIRST)
+                    c[u] = dy[(crow + xc) * 16 + i];
+                else
+                    cb[u] = reinterpret_cast<const unsigned short*>(A)[(crow + xc) * 16 + i];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const long long p = grow[t] + std::min(std::max(x + ox[t], 0), d.nx - 1);
+                    if constexpr (FIRST)
+                        rv[u][t] = r[p];
+                    else
+                        g[u][t] = dy[p];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (x0 + 4 * u >= d.nx) break;
+                const int x = x0 + 4 * u + kq;
+                if constexpr (!FIRST) c[u] = __uint_as_float((unsigned)cb[u] << 16);
+                const float cv = x < d.nx ? c[u] : 0.f;
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    if constexpr (FIRST) g[u][t] = (float)bf16_via_f32(in_scale * rv[u][t]);
+                    const int xx = x + ox[t];
+                    const float gv = rok[t] && x < d.nx && xx >= 0 && xx < d.nx ? g[u][t] : 0.f;
+                    acc[t] = FIRST ? __builtin_amdgcn_mfma_f32_16x16x4f32(gv, cv, acc[t], 0, 0, 0)
+                                   : __builtin_amdgcn_mfma_f32_16x16x4f32(cv, gv, acc[t], 0, 0, 0);
+                }
+            }
+        }
+    }
+    dw_block_sum<2>(acc, red, part + (long long)blockIdx.x * 512, w, lane);
+}
+
+// How the elements of a group's partial sums lie in the gradient.
+enum DwLayout { DW_CONV, DW_ROW_TAPS, DW_COL_TAPS, DW_PLAIN };
+
+// grad (+)= sum over blocks of part[group][block][E], fixed order: 32 elements
+// of a block, eight slices of the partials each (one thread per element took
+// 35 us for 256 partials, the latency of one after the other).
+__global__ __launch_bounds__(256) void dw_reduce(const float* __restrict__ part, int nblk, int E, int layout, int CI,
+                                                 int CO, int tpw, float* __restrict__ grad, int accumulate) {
+    __shared__ float sh[8][32];
+    const int l = threadIdx.x & 31, sl = threadIdx.x >> 5;
+    const int e = blockIdx.x * 32 + l;
     float s = 0.f;
-    for (int b = 0; b < nblk; ++b) s += part[((long long)tap * nblk + b) * NP + pidx];
-    const int co = pidx / CI, ci = pidx % CI;
-    float* g = grad + (long long)co * 27 * CI + tap * CI + ci;
-    *g = accumulate ? *g + s : s;
+    if (e < E) {
+        const float* p = part + (long long)blockIdx.y * nblk * E + e;
+#pragma unroll 4
+        for (int b = sl; b < nblk; b += 8) s += p[(long long)b * E];
+    }
+    sh[sl][l] = s;
+    __syncthreads();
+    if (sl != 0 || e >= E) return;
+    for (int q = 1; q < 8; ++q) s += sh[q][l];
+    const int lane = e & 63, row = 4 * (lane >> 4) + ((e >> 6) & 3), col = lane & 15, tile = e >> 8;
+    int at = e;
+    if (layout == DW_CONV) {
+        const int mt = CI / 16, nt = CO / 16;
+        const int n = tile % nt, m = (tile / nt) % mt, tap = (int)blockIdx.y * tpw + tile / (nt * mt);
+        at = (nt * col + n) * 27 * CI + tap * CI + mt * row + m;
+    } else if (layout == DW_ROW_TAPS) {
+        const int tap = 16 * tile + row;
+        if (tap >= 27) return;
+        at = col * 27 + tap;
+    } else if (layout == DW_COL_TAPS) {
+        const int tap = 16 * tile + col;
+        if (tap >= 27) return;
+        at = tap * CI + row;
+    }
+    grad[at] = accumulate ? grad[at] + s : s;
 }
 
 // dg[v][ci] = sum_tap W[tap][ci] * dz[v - tap]   (output layer, one channel)
@@ -1403,15 +1585,6 @@ __global__ __launch_bounds__(256) void proj_grad_partial(const bf16* __restrict_
     }
 }
 
-__global__ void proj_grad_reduce(const float* __restrict__ part, int nblk, int C, float* __restrict__ grad,
-                                 int accumulate) {
-    const int c = threadIdx.x;
-    if (c >= C) return;
-    float s = 0.f;
-    for (int b = 0; b < nblk; ++b) s += part[(long long)b * C + c];
-    grad[c] = accumulate ? grad[c] + s : s;
-}
-
 // ... and its adjoint dg[V][c] = wp[c] dgz[V]
 __global__ void proj_adjoint(const float* __restrict__ dgz, const float* __restrict__ wp, long long n, int C,
                              float* __restrict__ dg) {
@@ -1472,6 +1645,74 @@ __global__ void anorm_loss(const double* __restrict__ z, const double* __restric
 __global__ void scale_to_f32(const double* __restrict__ a, double s, float* __restrict__ b, long long n) {
     const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (q < n) b[q] = (float)(s * a[q]);
+}
+
+// The layouts the network reads, from the flat FP32 master weights.
+struct PrepLayers {
+    static constexpr int kMax = 12;  // first, enc1, up to 8 of the bottleneck, dec1
+    struct {
+        long long m, w, wt;
+        int ci, co, kp, kpt;
+    } l[kMax];
+    int n;
+};
+
+// blockIdx.y: a 27-tap layer, forward [co][kp] and transposed [ci][kpt], zero
+// padded; the last one the projection, output and composed weights
+__global__ __launch_bounds__(256) void prep_weights(const float* __restrict__ master, const PrepLayers P, long long m_proj,
+                                                    long long m_out, int c0, bf16* __restrict__ w, bf16* __restrict__ wt,
+                                                    float* __restrict__ w_proj, float* __restrict__ w_out,
+                                                    float* __restrict__ w_comp, bf16* __restrict__ w_pool) {
+    const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+    if ((int)blockIdx.y < P.n) {
+        const auto& L = P.l[blockIdx.y];
+        const float* m = master + L.m;
+        const int K = 27 * L.ci;
+        if (e < (long long)L.kp * L.co) {
+            const int co = (int)(e / L.kp), k = (int)(e % L.kp);
+            w[L.w + e] = k < K ? (bf16)m[(long long)co * K + k] : (bf16)0.f;
+        }
+        // transposed: Wt[ci][tap' * co + c] = W[c][(26 - tap') * ci + ci]
+        if (L.ci > 1 && e < (long long)L.kpt * L.ci) {
+            const int ci = (int)(e / L.kpt), k = (int)(e % L.kpt), tp = k / L.co, c = k % L.co;
+            wt[L.wt + e] = k < 27 * L.co ? (bf16)m[(long long)c * K + (26 - tp) * L.ci + ci] : (bf16)0.f;
+        }
+        return;
+    }
+    const float* m0 = master + P.l[0].m;  // W0[c][tap], ci = 1
+    const float* mo = master + m_out;
+    if (e < c0) w_proj[e] = (float)(bf16)master[m_proj + e];
+    if (e < 27 * c0) w_out[e] = (float)(bf16)mo[e];
+    // composed output stencil: Wc[t1 + t2] += sum_c W_out[t1][c] W0[c][t2]
+    // (bf16-rounded factors, FP64 sums, one rounding to FP32)
+    if (e < 125) {
+        const int ez = (int)e / 25, ey = ((int)e / 5) % 5, ex = (int)e % 5;
+        double sum = 0.0;
+        for (int t1 = 0; t1 < 27; ++t1) {
+            const int z = ez - t1 / 9, y = ey - (t1 / 3) % 3, x = ex - t1 % 3;
+            if (z < 0 || z > 2 || y < 0 || y > 2 || x < 0 || x > 2) continue;
+            double acc = 0.0;
+            for (int c = 0; c < c0; ++c)
+                acc += (double)(float)(bf16)mo[t1 * c0 + c] * (double)(float)(bf16)m0[c * 27 + 9 * z + 3 * y + x];
+            sum += acc;
+        }
+        w_comp[e] = (float)sum;
+    }
+    // pooled first conv: Wp[c][s] = 1/8 sum_o W0[c][s - o], s = (sz, sy, sx) in
+    // 0..3 (k = 16 sz + 4 sy + sx), o in {0, 1}^3; as a BF16 pair hi + lo
+    if (e < 16 * 64) {
+        const int ch = (int)e / 64, k = (int)e % 64, sz = k / 16, sy = (k / 4) % 4, sx = k % 4;
+        double acc = 0.0;
+        for (int o = 0; o < 8; ++o) {
+            const int tz = sz - (o >> 2), ty = sy - ((o >> 1) & 1), tx = sx - (o & 1);
+            if (tz < 0 || tz > 2 || ty < 0 || ty > 2 || tx < 0 || tx > 2) continue;
+            acc += (double)(float)(bf16)m0[ch * 27 + 9 * tz + 3 * ty + tx];
+        }
+        acc *= 0.125;
+        const bf16 hi = (bf16)(float)acc;
+        w_pool[e] = hi;
+        w_pool[16 * 64 + e] = (bf16)(float)(acc - (double)(float)hi);
+    }
 }
 
 __global__ void adam_kernel(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
@@ -1573,6 +1814,7 @@ struct kvs_unet {
     bf16* gb = nullptr;         // bf16 staging of a gradient (conv^T input)
     float* dzf = nullptr;
     double* dz_raw = nullptr;
+    double* zt = nullptr;       // network output of a training sample
     double* part = nullptr;
     float* wpart = nullptr;
     int64_t wpart_n = 0;
@@ -1603,6 +1845,7 @@ void unet_free_train(kvs_unet* u) {
     u->dbott.clear();
     ufree(u->gb);
     ufree(u->dz_raw);
+    ufree(u->zt);
     ufree(u->part);
     ufree(u->wpart);
     u->wpart_n = 0;
@@ -1662,6 +1905,7 @@ hipError_t unet_ensure_train(kvs_unet* u, Dims d) {
     if (e == hipSuccess) e = hipMalloc(&u->gb, sizeof(bf16) * std::max(n1 * u->c1, n2 * u->c2));
     if (e == hipSuccess) e = hipMalloc(&u->dzf, sizeof(float) * n0);
     if (e == hipSuccess) e = hipMalloc(&u->dz_raw, sizeof(double) * n0);
+    if (e == hipSuccess) e = hipMalloc(&u->zt, sizeof(double) * n0);
     if (e == hipSuccess) e = hipMalloc(&u->part, sizeof(double) * 2 * nblocks256(n0));
     if (e != hipSuccess) {
         unet_free_train(u);
@@ -1796,35 +2040,59 @@ int64_t kvs_unet_out_blocks(const kvs_grid& g) {
 
 namespace {
 
-// dispatch of the weight-gradient reduction
+// room for n partial sums of a weight gradient
+hipError_t dw_room(kvs_unet* u, int64_t n) {
+    if (n <= u->wpart_n) return hipSuccess;
+    ufree(u->wpart);
+    u->wpart_n = 0;
+    const hipError_t e = hipMalloc(&u->wpart, sizeof(float) * n);
+    if (e == hipSuccess) u->wpart_n = n;
+    return e;
+}
+
+// Weight gradient of one conv.  About 2048 wavefronts, two on a SIMD, over
+// (tap groups) x (blocks of eight wavefronts, a row each at least): one tap a
+// wavefront where a tap is 8 or 16 tiles, else the three of an x triple, which
+// share dy.  64^3 input, us, before (one thread per weight
+// and 64 voxels in LDS at a time, a block per tap) and now:
+//   1 -> 16, 16 -> 1 at 64^3      115, 267  ->  16, 17
+//   16 -> 32, 32 -> 16 at 32^3     70, 79   ->  32, 33
+//   32 -> 64, 64 -> 32 at 16^3     42, 59   ->  14, 15
+//   64 -> 64 at 16^3               63       ->  22
+// and 35 -> 4.5 for each reduction.  Floor of the largest, 0.45 G products at
+// the matrix cores' FP32 rate: 6 us; the rest is the latency of the loads of a
+// step and the filling and summing of short launches.
 hipError_t launch_dw(kvs_unet* u, int ci, int co, bool first, const bf16* A, const double* r,
                      double in_scale, Dims d, int dil, const float* dy, int64_t m_off, int accumulate, hipStream_t s) {
-    const int nblk = (int)std::min<long long>(256, (d.n() + 63) / 64);
-    const int64_t need = 27LL * nblk * ci * co;
-    if (need > u->wpart_n) {
-        ufree(u->wpart);
-        hipError_t e = hipMalloc(&u->wpart, sizeof(float) * need);
-        if (e != hipSuccess) return e;
-        u->wpart_n = need;
-    }
-    const dim3 grid(nblk, 27);
-#define KVS_DW_CASE(CI_, CO_, F_)                                                                                  \
-    if (ci == CI_ && co == CO_ && first == F_) {                                                                   \
-        hipLaunchKernelGGL((dw_partial<CI_, CO_, F_>), grid, dim3(256), 0, s, A, r, in_scale, d, dil, dy, u->wpart); \
-    } else
-    KVS_DW_CASE(1, 16, true)
-    KVS_DW_CASE(16, 32, false)
-    KVS_DW_CASE(32, 64, false)
-    KVS_DW_CASE(64, 64, false)
-    KVS_DW_CASE(64, 32, false)
-    KVS_DW_CASE(32, 16, false)
-    KVS_DW_CASE(16, 16, false)
-    KVS_DW_CASE(16, 1, false) { return hipErrorInvalidValue; }
-#undef KVS_DW_CASE
-    hipError_t e = hipGetLastError();
+    const long long rows = (long long)d.ny * d.nz;
+    const bool taps = ci == 1 || co == 1;
+    if (taps && dil != 1) return hipErrorInvalidValue;
+    const int tpw = !taps && ci * co <= 512 ? 3 : 1, groups = taps ? 1 : 27 / tpw;
+    const int E = taps ? 512 : tpw * ci * co;
+    const int nblk = (int)std::min<long long>((256 + groups - 1) / groups, (rows + kDwWaves - 1) / kDwWaves);
+    hipError_t e = dw_room(u, (int64_t)groups * nblk * E);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(dw_reduce, dim3(nblocks256(27LL * ci * co)), dim3(256), 0, s, u->wpart, nblk, ci, co,
-                       u->grad + m_off, accumulate);
+    const dim3 grid(nblk, groups), block(64 * kDwWaves);
+#define KVS_DW_CASE(CI_, CO_, T_)                                                                     \
+    if (ci == CI_ && co == CO_) {                                                                     \
+        hipLaunchKernelGGL((dw_mfma<CI_, CO_, T_>), grid, block, 0, s, A, d, dil, dy, u->wpart);      \
+    } else
+    KVS_DW_CASE(16, 32, 3)
+    KVS_DW_CASE(32, 16, 3)
+    KVS_DW_CASE(32, 64, 1)
+    KVS_DW_CASE(64, 32, 1)
+    KVS_DW_CASE(64, 64, 1)
+#undef KVS_DW_CASE
+    if (ci == 1 && co == 16 && first)
+        hipLaunchKernelGGL(dw_taps<true>, grid, block, 0, s, A, r, in_scale, d, dy, u->wpart);
+    else if (ci == 16 && co == 1 && !first)
+        hipLaunchKernelGGL(dw_taps<false>, grid, block, 0, s, A, r, in_scale, d, dy, u->wpart);
+    else
+        return hipErrorInvalidValue;
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(dw_reduce, dim3((E + 31) / 32, groups), dim3(256), 0, s, u->wpart, nblk, E,
+                       ci == 1 ? DW_ROW_TAPS : co == 1 ? DW_COL_TAPS : DW_CONV, ci, co, tpw, u->grad + m_off,
+                       accumulate);
     return hipGetLastError();
 }
 
@@ -1852,14 +2120,10 @@ hipError_t unet_backward(kvs_unet* u, const double* r, double in_scale, Dims d, 
     // projection gz = g1 . wp
     {
         const int nblk = (int)std::min<long long>(256, (d1.n() + 15) / 16);
-        if ((long long)nblk * c0 > u->wpart_n) {
-            ufree(u->wpart);
-            if ((e = hipMalloc(&u->wpart, sizeof(float) * nblk * c0)) != hipSuccess) return e;
-            u->wpart_n = (int64_t)nblk * c0;
-        }
+        if ((e = dw_room(u, (int64_t)nblk * c0)) != hipSuccess) return e;
         hipLaunchKernelGGL(proj_grad_partial<16>, dim3(nblk), dim3(256), 0, s, u->g1, u->dgz, d1.n(), u->wpart);
-        hipLaunchKernelGGL(proj_grad_reduce, dim3(1), dim3(64), 0, s, u->wpart, nblk, c0, u->grad + u->m_off[lp],
-                           accumulate);
+        hipLaunchKernelGGL(dw_reduce, dim3(1), dim3(256), 0, s, u->wpart, nblk, c0, DW_PLAIN, c0, 1, 1,
+                           u->grad + u->m_off[lp], accumulate);
         hipLaunchKernelGGL(proj_adjoint, dim3(nblocks256(d1.n() * c0)), dim3(256), 0, s, u->dgz, u->w_proj, d1.n(), c0,
                            u->dg1);
     }
@@ -1911,66 +2175,26 @@ kvs_status ufail(kvs_unet* u, kvs_status s, const std::string& m) {
     return s;
 }
 
-// host master -> device master, bf16 forward / transposed layouts, fp32 out
+// BF16 forward and transposed layouts, FP32 projection, output and composed
+// weights of the device's master weights, on the legacy default stream (after
+// what other streams still read) and complete on return.  A host loop over the
+// 0.3 M weights and seven copies took 4.1 ms of every training step.
 kvs_status upload_weights(kvs_unet* u) {
-    std::vector<bf16> wb((size_t)u->n_w, (bf16)0.f), wtb((size_t)std::max<int64_t>(u->n_wt, 1), (bf16)0.f);
     const int nl = (int)u->layers.size();
-    for (int l = 0; l < nl - 2; ++l) {
+    PrepLayers P{};
+    P.n = nl - 2;
+    if (P.n > PrepLayers::kMax) return ufail(u, KVS_EINVAL, "too many layers");
+    int64_t most = 16 * 64;
+    for (int l = 0; l < P.n; ++l) {
         const UnetLayerDesc& L = u->layers[(size_t)l];
-        const float* m = u->host_master.data() + u->m_off[(size_t)l];
-        const int64_t K = 27LL * L.ci, kp = u->kp[(size_t)l], kpt = u->kpt[(size_t)l];
-        for (int co = 0; co < L.co; ++co)
-            for (int64_t k = 0; k < K; ++k) wb[(size_t)(u->w_off[(size_t)l] + co * kp + k)] = (bf16)m[co * K + k];
-        if (L.ci == 1) continue;
-        // transposed: Wt[ci][tap' * co + c] = W[c][(26 - tap') * ci + ci]
-        for (int ci = 0; ci < L.ci; ++ci)
-            for (int tp = 0; tp < 27; ++tp)
-                for (int c = 0; c < L.co; ++c)
-                    wtb[(size_t)(u->wt_off[(size_t)l] + ci * kpt + tp * L.co + c)] =
-                        (bf16)m[(int64_t)c * K + (26 - tp) * L.ci + ci];
+        P.l[l] = {(long long)u->m_off[(size_t)l], (long long)u->w_off[(size_t)l], (long long)u->wt_off[(size_t)l],
+                  L.ci, L.co, (int)u->kp[(size_t)l], (int)u->kpt[(size_t)l]};
+        most = std::max(most, std::max(u->kp[(size_t)l] * L.co, u->kpt[(size_t)l] * L.ci));
     }
-    std::vector<float> wpj((size_t)u->c0);
-    const float* mp = u->host_master.data() + u->m_off[(size_t)(nl - 2)];
-    for (size_t q = 0; q < wpj.size(); ++q) wpj[q] = (float)(bf16)mp[q];
-    std::vector<float> wo((size_t)27 * u->c0);
-    const float* mo = u->host_master.data() + u->m_off[(size_t)(nl - 1)];
-    for (size_t q = 0; q < wo.size(); ++q) wo[q] = (float)(bf16)mo[q];
-    // composed output stencil: Wc[t1 + t2] += sum_c W_out[t1][c] W0[c][t2]
-    // (bf16-rounded factors, FP64 sums, one rounding to FP32)
-    std::vector<double> wc(125, 0.0);
-    const float* m0 = u->host_master.data() + u->m_off[0];  // W0[c][tap], ci = 1
-    for (int t1 = 0; t1 < 27; ++t1)
-        for (int t2 = 0; t2 < 27; ++t2) {
-            const int dz = t1 / 9 + t2 / 9, dy = (t1 / 3) % 3 + (t2 / 3) % 3, dx = t1 % 3 + t2 % 3;
-            double acc = 0.0;
-            for (int c = 0; c < u->c0; ++c) acc += (double)wo[(size_t)(t1 * u->c0 + c)] * (double)(float)(bf16)m0[c * 27 + t2];
-            wc[(size_t)(25 * dz + 5 * dy + dx)] += acc;
-        }
-    std::vector<float> wcf(wc.begin(), wc.end());
-    // pooled first conv: Wp[c][s] = 1/8 sum_o W0[c][s - o], s = (sz, sy, sx) in
-    // 0..3 (k = 16 sz + 4 sy + sx), o in {0, 1}^3; as a BF16 pair hi + lo
-    std::vector<bf16> wpl((size_t)2 * 16 * 64);
-    for (int ch = 0; ch < 16; ++ch)
-        for (int k = 0; k < 64; ++k) {
-            const int sz = k / 16, sy = (k / 4) % 4, sx = k % 4;
-            double acc = 0.0;
-            for (int o = 0; o < 8; ++o) {
-                const int tz = sz - (o >> 2), ty = sy - ((o >> 1) & 1), tx = sx - (o & 1);
-                if (tz < 0 || tz > 2 || ty < 0 || ty > 2 || tx < 0 || tx > 2) continue;
-                acc += (double)(float)(bf16)m0[ch * 27 + 9 * tz + 3 * ty + tx];
-            }
-            acc *= 0.125;
-            const bf16 hi = (bf16)(float)acc;
-            wpl[(size_t)ch * 64 + k] = hi;
-            wpl[(size_t)16 * 64 + ch * 64 + k] = (bf16)(float)(acc - (double)(float)hi);
-        }
-    if (hipMemcpy(u->w, wb.data(), sizeof(bf16) * wb.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        (u->n_wt > 0 && hipMemcpy(u->wt, wtb.data(), sizeof(bf16) * u->n_wt, hipMemcpyHostToDevice) != hipSuccess) ||
-        hipMemcpy(u->w_proj, wpj.data(), sizeof(float) * wpj.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(u->w_out, wo.data(), sizeof(float) * wo.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(u->w_comp, wcf.data(), sizeof(float) * wcf.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(u->w_pool, wpl.data(), sizeof(bf16) * wpl.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(u->master, u->host_master.data(), sizeof(float) * u->n_master, hipMemcpyHostToDevice) != hipSuccess)
+    hipLaunchKernelGGL(prep_weights, dim3(nblocks256(most), P.n + 1), dim3(256), 0, nullptr, u->master, P,
+                       (long long)u->m_off[(size_t)(nl - 2)], (long long)u->m_off[(size_t)(nl - 1)], u->c0, u->w, u->wt,
+                       u->w_proj, u->w_out, u->w_comp, u->w_pool);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess)
         return ufail(u, KVS_EDEVICE, "weight upload failed");
     return KVS_OK;
 }
@@ -2002,6 +2226,7 @@ kvs_status kvs_unet_create(const int32_t* channels, int32_t n_bottleneck, kvs_un
     ok = ok && hipMalloc(&u->w_pool, sizeof(bf16) * 2 * 16 * 64) == hipSuccess;
     for (float** p : {&u->master, &u->grad, &u->adam_m, &u->adam_v})
         ok = ok && hipMalloc(p, sizeof(float) * u->n_master) == hipSuccess;
+    ok = ok && hipMemset(u->master, 0, sizeof(float) * u->n_master) == hipSuccess;
     ok = ok && hipMemset(u->grad, 0, sizeof(float) * u->n_master) == hipSuccess;
     ok = ok && hipMemset(u->adam_m, 0, sizeof(float) * u->n_master) == hipSuccess;
     ok = ok && hipMemset(u->adam_v, 0, sizeof(float) * u->n_master) == hipSuccess;
@@ -2059,6 +2284,8 @@ kvs_status kvs_unet_set_weights(kvs_unet* u, const float* w, int64_t n) {
     u->adam_t = 0;
     if (hipMemset(u->adam_m, 0, sizeof(float) * n) != hipSuccess || hipMemset(u->adam_v, 0, sizeof(float) * n) != hipSuccess)
         return ufail(u, KVS_EDEVICE, "reset of the optimiser state failed");
+    if (hipMemcpy(u->master, w, sizeof(float) * n, hipMemcpyHostToDevice) != hipSuccess)
+        return ufail(u, KVS_EDEVICE, "weight upload failed");
     return upload_weights(u);
 }
 
@@ -2111,8 +2338,7 @@ kvs_status kvs_unet_train_sample(kvs_unet* u, const double* b, const double* xs,
     hipStream_t s = (hipStream_t)stream;
     NetCtl ctl{nullptr, nullptr, nullptr, 1.0, 1.0};
     hipError_t e = unet_ensure_train(u, d);
-    double* z = nullptr;
-    if (e == hipSuccess) e = hipMalloc(&z, sizeof(double) * d.n());
+    double* z = u->zt;
     if (e == hipSuccess) e = kvs_unet_apply(u, b, ctl, z, d, s, true);
     const int nb = nblocks256(d.n());
     std::vector<double> part((size_t)2 * nb);
@@ -2127,17 +2353,14 @@ kvs_status kvs_unet_train_sample(kvs_unet* u, const double* b, const double* xs,
         eAe += part[(size_t)2 * q];
         xAx += part[(size_t)2 * q + 1];
     }
-    if (e == hipSuccess && !(xAx > 0.0)) {
-        (void)hipFree(z);
-        return ufail(u, KVS_EINVAL, "training target has zero A-norm");
-    }
+    if (e == hipSuccess && !(xAx > 0.0)) return ufail(u, KVS_EINVAL, "training target has zero A-norm");
     // L = e.Ae / xAx, dL/dz = 2 A e / xAx
     if (e == hipSuccess) {
         hipLaunchKernelGGL(scale_to_f32, dim3(nb), dim3(256), 0, s, u->dz_raw, 2.0 / xAx, u->dzf, d.n());
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = unet_backward(u, b, 1.0, d, accumulate, s);
-    if (z) (void)hipFree(z);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);  // b and the gradient are the caller's on any stream
     if (e != hipSuccess) return ufail(u, KVS_EDEVICE, std::string("unet train: ") + hipGetErrorString(e));
     if (loss) *loss = eAe / xAx;
     return KVS_OK;
