@@ -506,11 +506,18 @@ hipError_t capture_t(kvs_batch* b, int64_t nsteps, const std::vector<uint8_t>& p
 // one workgroup's LDS, a batch run is one launch of one block per instance
 // that advances its instance through all the steps in the kernel: the state
 // lives in LDS for the whole run, the block's threads own fixed interior
-// cells, and two block barriers per step separate reading the old state from
-// writing the new one; probe values are written after every step.  The
-// per-cell arithmetic is the step kernel's (same operand order, sponge
-// factors and FP32 reciprocal), so one launch replaces two launches per step
-// and the run is bound by the latency of a step, not by launches.
+// cells, and block barriers separate reading the old state from writing the
+// new one; probe values are written after every step.  The per-cell arithmetic
+// is the step kernel's (same operand order, sponge factors and FP32
+// reciprocal), so one launch replaces two launches per step and the run is
+// bound by the latency of a step, not by launches.
+//
+// A step is one chain: LDS reads, the update of a thread, LDS writes, barrier.
+// Where three times the threads fit a block, each component of a cell has its
+// own thread (SPLIT): the update is a third as long and the SIMDs are evenly
+// filled (299 cells are five wavefronts on four SIMDs, as components fifteen).
+// A line keeps only its own nodes in LDS, twice, and needs one barrier a step.
+// 16 lines of 301 nodes, 16000 steps: 6.70 -> 5.07 ms (0.32 us a step).
 constexpr int kSmallMaxThreads = 1024;
 constexpr int kSmallChunk = 64;  // steps whose envelope and probe values are staged in LDS at a time
 constexpr size_t kSmallMaxLds = 150 * 1024;
@@ -518,13 +525,17 @@ constexpr size_t kSmallMaxLds = 150 * 1024;
 // LINE: every instance is a line (ny = nz = 3): the y and z neighbours of an
 // interior node lie on the Dirichlet layer and are exactly 0, so they are
 // taken as the constant 0 instead of read (the same arithmetic).
-template <typename T, bool VISC, int CPT, bool LINE>
+template <typename T, bool VISC, int CPT, bool LINE, bool SPLIT>
 __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const BatchInst<T>* inst, const long long* probes,
                                                                        const long long* probe_first, int np, int comp,
                                                                        double* traces, long long step0,
                                                                        long long nsteps) {
     extern __shared__ __align__(16) unsigned char small_lds[];
-    const int nthr = blockDim.x;
+    constexpr int NC = SPLIT ? 1 : 3;    // components of a thread, from cb on
+    constexpr int NB = LINE ? 2 : 1;     // copies of the state
+    const int nthr = blockDim.x, ncell = SPLIT ? nthr / 3 : nthr;
+    const int cb = SPLIT ? __builtin_amdgcn_readfirstlane(threadIdx.x / (unsigned)ncell) : 0;
+    const int tcell = (int)threadIdx.x - cb * ncell;
     // everything the step loop needs is read once: the loop's stores to the
     // traces would otherwise make the compiler re-read it every step
     const StepArgs<T> a = inst[blockIdx.x].a[0];  // parity 0: the buffers current at the start of the run
@@ -534,35 +545,46 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
     const genv_t env = (genv_t)inst[blockIdx.x].env;
     const long long n_env = inst[blockIdx.x].n_env;
     const int N = (int)a.N;
-    T* su = reinterpret_cast<T*>(small_lds);  // [3][N]
-    T* sw = su + 3 * N;                        // [3][N]
-    T* senv = sw + 3 * N;                      // [kSmallChunk]: the chunk's envelope values
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const int S = LINE ? nx : N;                // nodes of a component in LDS
+    T* su = reinterpret_cast<T*>(small_lds);    // [NB][3][S]
+    T* sw = su + NB * 3 * S;                    // [NB][3][S]
+    T* senv = sw + NB * 3 * S;                  // [kSmallChunk]: the chunk's envelope values, and a 0
     const long long pf = np > 0 ? probe_first[blockIdx.x] : 0;
     const int npi = np > 0 ? (int)(probe_first[blockIdx.x + 1] - pf) : 0;
-    T* strace = senv + kSmallChunk;                                     // [kSmallChunk][npi]: probe values
+    T* strace = senv + kSmallChunk + 1;                                 // [kSmallChunk][npi]: probe values
     int* sprobe = reinterpret_cast<int*>(strace + kSmallChunk * npi);  // this instance's probe cells
-    for (int q = threadIdx.x; q < 3 * N; q += nthr) {
-        su[q] = a.u[q];
-        sw[q] = a.w[q];
+    const int row = LINE ? nx * (1 + ny) : 0;  // node 0 of the row kept
+    for (int q = threadIdx.x; q < 3 * S; q += nthr) {
+        const int c = q / S, g = c * N + row + q % S;
+#pragma unroll
+        for (int h = 0; h < NB; ++h) {
+            su[h * 3 * S + q] = a.u[g];
+            sw[h * 3 * S + q] = a.w[g];
+        }
     }
-    for (int p = threadIdx.x; p < npi; p += nthr) sprobe[p] = comp * N + (int)probes[2 * (pf + p) + 1];
-    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    if (threadIdx.x == 0) senv[kSmallChunk] = T(0);
+    for (int p = threadIdx.x; p < npi; p += nthr) {
+        const int q = (int)probes[2 * (pf + p) + 1];
+        // off the row kept: a node of the Dirichlet layer, 0
+        sprobe[p] = !LINE ? comp * N + q : q >= row && q < row + nx ? comp * S + q - row : -1;
+    }
     const int nxi = nx - 2, nyi = ny - 2, nint = nxi * nyi * (nz - 2);
     const int sy = nx, sz = nx * ny;
     // owned cells: their index, sponge factors, f_S and own u, w (registers)
     int cell[CPT];
-    T a1[CPT], a2[CPT], fs[CPT][3], ur[CPT][3], wr[CPT][3];
+    T a1[CPT], a2[CPT], fs[CPT][NC], ur[CPT][NC], wr[CPT][NC];
 #pragma unroll
     for (int m = 0; m < CPT; ++m) {
-        const int t = threadIdx.x + m * nthr;
+        const int t = tcell + m * ncell;
         cell[m] = -1;
         a1[m] = a2[m] = T(0);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) fs[m][c] = ur[m][c] = wr[m][c] = T(0);
+        for (int c = 0; c < NC; ++c) fs[m][c] = ur[m][c] = wr[m][c] = T(0);
         if (t < nint) {
             const int i = 1 + t % nxi, j = 1 + (t / nxi) % nyi, k = 1 + t / (nxi * nyi);
             const int q = i + nx * (j + ny * k);
-            cell[m] = q;
+            cell[m] = q - row;
             const T r = a.L > 0 ? max(max(ramp<T>(i, nx, a.L, a.invL), ramp<T>(j, ny, a.L, a.invL)),
                                       ramp<T>(k, nz, a.L, a.invL))
                                 : T(0);
@@ -571,10 +593,10 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
             a1[m] = (T(1) - s) * inv1ps;
             a2[m] = a.crho0 * inv1ps;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                fs[m][c] = a.FS[c * a.N + q];
-                ur[m][c] = a.u[c * a.N + q];
-                wr[m][c] = a.w[c * a.N + q];
+            for (int c = 0; c < NC; ++c) {
+                fs[m][c] = a.FS[(cb + c) * a.N + q];
+                ur[m][c] = a.u[(cb + c) * a.N + q];
+                wr[m][c] = a.w[(cb + c) * a.N + q];
             }
         }
     }
@@ -592,13 +614,17 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
         lds_barrier();
         for (int sc = 0; sc < cn; ++sc) {
             const T gn = senv[sc];
+            const T* ru = su + (LINE ? (sc & 1) * 3 * S : 0);  // chunks are of even length but the last
+            const T* rw = sw + (LINE ? (sc & 1) * 3 * S : 0);
+            T* nu = su + (LINE ? (~sc & 1) * 3 * S : 0);
+            T* nw = sw + (LINE ? (~sc & 1) * 3 * S : 0);
 #pragma unroll
             for (int m = 0; m < CPT; ++m) {
                 if (cell[m] < 0) continue;
                 const int c0 = cell[m];
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const T* u = su + c * N;
+                for (int c = 0; c < NC; ++c) {
+                    const T* u = ru + (cb + c) * S;
                     const T uc = ur[m][c];
                     const T uyp = LINE ? T(0) : u[c0 + sy], uym = LINE ? T(0) : u[c0 - sy];
                     const T uzp = LINE ? T(0) : u[c0 + sz], uzm = LINE ? T(0) : u[c0 - sz];
@@ -606,7 +632,7 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
                           + gz * (uzp - uc) - gz * (uc - uzm);
                     const T wc = wr[m][c];
                     if constexpr (VISC) {
-                        const T* w = sw + c * N;
+                        const T* w = rw + (cb + c) * S;
                         const T wyp = LINE ? T(0) : w[c0 + sy], wym = LINE ? T(0) : w[c0 - sy];
                         const T wzp = LINE ? T(0) : w[c0 + sz], wzm = LINE ? T(0) : w[c0 - sz];
                         const T lw = (w[c0 + 1] + w[c0 - 1] - T(2) * wc) * ihx2 + (wyp + wym - T(2) * wc) * ihy2
@@ -619,38 +645,44 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
                     ur[m][c] = uc + wnew;
                 }
             }
-            lds_barrier();  // every read of the old state is done
+            if constexpr (!LINE) lds_barrier();  // every read of the old state is done
 #pragma unroll
             for (int m = 0; m < CPT; ++m)
                 if (cell[m] >= 0)
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        su[c * N + cell[m]] = ur[m][c];
-                        if constexpr (VISC) sw[c * N + cell[m]] = wr[m][c];
+                    for (int c = 0; c < NC; ++c) {
+                        nu[(cb + c) * S + cell[m]] = ur[m][c];
+                        if constexpr (VISC) nw[(cb + c) * S + cell[m]] = wr[m][c];
                     }
             lds_barrier();  // the new state is complete
-            for (int p = threadIdx.x; p < npi; p += nthr) strace[sc * npi + p] = su[sprobe[p]];
+            for (int p = threadIdx.x; p < npi; p += nthr) strace[sc * npi + p] = *(sprobe[p] >= 0 ? nu + sprobe[p] : senv + kSmallChunk);
         }
         lds_barrier();  // the chunk's probe values are complete
-        for (int q = threadIdx.x; q < cn * npi; q += nthr)
-            traces[(st0 + q / npi) * (long long)np + pf + q % npi] = (double)strace[q];
+        for (int r = threadIdx.x >> 6; r < cn; r += nthr >> 6)
+            for (int p = threadIdx.x & 63; p < npi; p += 64)
+                traces[(st0 + r) * (long long)np + pf + p] = (double)strace[r * npi + p];
         // the next chunk writes senv and strace only after the barrier that
         // follows its envelope load, i.e. after these reads
     }
-    // the run leaves the instance's state in the buffers current after nsteps
-    // (w in LDS is stale without viscosity: the registers hold it)
+    // the run leaves the instance's state in the buffers current after nsteps:
+    // the cells from the registers, the Dirichlet layer as it was
     T* du = (nsteps & 1) ? a.un : const_cast<T*>(a.u);
     T* dw = (nsteps & 1) ? a.wn : const_cast<T*>(a.w);
+    if (nsteps & 1)
+        for (int q = threadIdx.x; q < 3 * N; q += nthr) {
+            const int n = q % N, i = n % nx, j = (n / nx) % ny, k = n / (nx * ny);
+            if (i >= 1 && i <= nx - 2 && j >= 1 && j <= ny - 2 && k >= 1 && k <= nz - 2) continue;
+            du[q] = a.u[q];
+            dw[q] = a.w[q];
+        }
 #pragma unroll
     for (int m = 0; m < CPT; ++m)
         if (cell[m] >= 0)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) sw[c * N + cell[m]] = wr[m][c];
-    lds_barrier();
-    for (int q = threadIdx.x; q < 3 * N; q += nthr) {
-        du[q] = su[q];
-        dw[q] = sw[q];
-    }
+            for (int c = 0; c < NC; ++c) {
+                du[(cb + c) * a.N + row + cell[m]] = ur[m][c];
+                dw[(cb + c) * a.N + row + cell[m]] = wr[m][c];
+            }
 }
 
 // LDS of the persistent kernel: the state (6 N values), a chunk's envelope
@@ -661,7 +693,7 @@ size_t small_lds_bytes(const kvs_batch* b, const kvs_ctx* c) {
     int64_t most = 0;
     for (size_t i = 0; i + 1 < b->probe_first.size(); ++i)
         most = std::max<int64_t>(most, b->probe_first[i + 1] - b->probe_first[i]);
-    return (6 * (size_t)c->N + kSmallChunk * (1 + (size_t)most)) * sizeof(T) + sizeof(int) * (size_t)most;
+    return (6 * (size_t)c->N + kSmallChunk * (1 + (size_t)most) + 1) * sizeof(T) + sizeof(int) * (size_t)most;
 }
 
 // Threads per workgroup (a multiple of 64, at most 1024, enough for one
@@ -682,13 +714,13 @@ bool small_fits(const kvs_batch* b, int* cpt, int* threads) {
     return true;
 }
 
-template <typename T, bool VISC, int CPT, bool LINE>
+template <typename T, bool VISC, int CPT, bool LINE, bool SPLIT = false>
 hipError_t launch_small_shape(kvs_batch* b, int64_t nsteps, int threads) {
     size_t lds = 0;
     for (const kvs_ctx* c : b->inst) lds = std::max(lds, small_lds_bytes<T>(b, c));
     static bool attr_set = false;  // one attribute call per instantiation
     if (!attr_set) {
-        const hipError_t e = hipFuncSetAttribute((const void*)batch_small_kernel<T, VISC, CPT, LINE>,
+        const hipError_t e = hipFuncSetAttribute((const void*)batch_small_kernel<T, VISC, CPT, LINE, SPLIT>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmallMaxLds);
         if (e != hipSuccess) return e;
         attr_set = true;
@@ -696,7 +728,7 @@ hipError_t launch_small_shape(kvs_batch* b, int64_t nsteps, int threads) {
     const int np = (int)b->probe_inst.size();
     const long long* pr = static_cast<const long long*>(b->dev_probes);
     double* tr = np > 0 ? b->traces + b->trace_steps * np : nullptr;
-    hipLaunchKernelGGL((batch_small_kernel<T, VISC, CPT, LINE>), dim3((unsigned)b->inst.size()), dim3(threads), lds,
+    hipLaunchKernelGGL((batch_small_kernel<T, VISC, CPT, LINE, SPLIT>), dim3((unsigned)b->inst.size()), dim3(SPLIT ? 3 * threads : threads), lds,
                        b->stream, static_cast<const BatchInst<T>*>(b->dev_params), pr, np > 0 ? pr + 2 * np : nullptr,
                        np, b->comp, tr, (long long)b->step, (long long)nsteps);
     return hipGetLastError();
@@ -706,7 +738,9 @@ template <typename T, bool VISC>
 hipError_t launch_small(kvs_batch* b, int64_t nsteps, int cpt, int threads) {
     bool line = true;
     for (const kvs_ctx* c : b->inst) line = line && c->grid.ny == 3 && c->grid.nz == 3;
+    const bool split = cpt == 1 && 3 * threads <= kSmallMaxThreads;
     if (line) {
+        if (split) return launch_small_shape<T, VISC, 1, true, true>(b, nsteps, threads);
         switch (cpt) {
             case 1: return launch_small_shape<T, VISC, 1, true>(b, nsteps, threads);
             case 2: return launch_small_shape<T, VISC, 2, true>(b, nsteps, threads);
