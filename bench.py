@@ -27,10 +27,10 @@ roofline: the dominant FDTD kernel over its HIP-event-timed launches,
           the cell-updates one launch processes, over its mean launch
           duration, against 8 TB/s.  By default that kernel is the two-step
           kernel (two cell-updates per cell and launch; it moves 60 B per two
-          updates and is limited by vector-ALU issue: limited_by, and alu =
+          updates and is limited by the latency of a plane: limited_by, and alu =
           its algorithmic FP32 flop rate, 147 flop per cell-update, against
-          the 78.6 TFLOP/s FMA peak without packed FP32); the one-step push
-          launches are listed beside it.  With --step-blocking 1 it is the
+          the 78.6 TFLOP/s FMA peak without packed FP32); one-step launches,
+          if any, are listed beside it.  With --step-blocking 1 it is the
           one-step kernel.  stream_gbs / frac_of_stream: a stream with the
           one-step kernel's 9 reads and 6 writes per cell and no stencil,
           measured in the same run (the ceiling of any one-step kernel);
@@ -71,22 +71,22 @@ HBM_PEAK_GBS = 8000.0
 # scaled by what it reads for a plain copy of known size (--copy-calibration):
 # FETCH_SIZE reports half of the bytes a copy reads, WRITE_SIZE all of the
 # bytes it writes.  A changed source voids the figures (traffic -> null).
-STEP_SOURCE_SHA = "f26c91bb5db918abca9fc803284f993aa0fe815a66b95bb68a2d2f50a855e0e9"
+STEP_SOURCE_SHA = "87f33e7e0ce90b1bd691da323d70afcd16b4918196681a00198047e267eda671"
 STEP_COUNTERS_KIB = {  # variant -> (FETCH_SIZE, WRITE_SIZE), mean of 6 dispatches
-    0: (423983.2, 390146.0),
-    1: (400448.2, 390146.0),
-    2: (322676.2, 390146.0),
-    3: (302672.6, 390146.3),
-    4: (361179.7, 390146.0),
-    5: (331166.7, 390146.0),
-    6: (304537.1, 390146.4),
-    7: (304696.8, 390146.7),
+    0: (423999.4, 390146.0),
+    1: (399713.7, 390146.0),
+    2: (323288.3, 390146.0),
+    3: (302645.5, 390146.0),
+    4: (356112.1, 390146.0),
+    5: (331558.2, 390146.0),
+    6: (304019.3, 390146.8),
+    7: (304534.2, 390148.7),
 }
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 # The same counters for the two-step kernel (step2_kernel, one launch = two
 # steps without force), taken on STEP2_SOURCES with SHA-256 STEP2_SOURCE_SHA.
-STEP2_SOURCE_SHA = "8a13c07d6ffc431d3d458ff01837be9fa8a7ec2b08a1f5cfc443e77c110124c7"
-STEP2_COUNTERS_KIB = (329607.6, 390148.0)  # (FETCH_SIZE, WRITE_SIZE), mean of 6 dispatches
+STEP2_SOURCE_SHA = "45e5eee20eccad1eeb402c42afa6ea6763343aab7f66ebb361d323f3f5b1b97e"
+STEP2_COUNTERS_KIB = (329553.0, 387138.1)  # (FETCH_SIZE, WRITE_SIZE), mean of 6 dispatches
 # Algorithmic FP32 arithmetic of one heterogeneous viscous cell-update of the
 # summed-form leapfrog (Sec. 3.1), an FMA counted as two: six harmonic face
 # moduli 2 G G' / (G + G') / h^2 (5 each, 30); the sponge factors s,
@@ -1114,7 +1114,7 @@ def main():
                 "frac_of_stream": one_gbs / stream_gbs if stream_gbs else None,
                 "note": "reference run of the one-step kernel after the timed region, 60 B per cell-update"}
     if n2 > 0:
-        # dominant kernel: two steps per launch, bound by vector-ALU issue
+        # dominant kernel: two steps per launch, bound by the latency of a plane
         t2 = ms2 / n2  # ms per two-step launch
         tflops = FLOP_PER_CELL_UPDATE * 2 * cells / (t2 * 1e-3) / 1e12
         hbm_eq = 60 * 2 * cells / (t2 * 1e-3) / 1e9
@@ -1132,7 +1132,7 @@ def main():
             "kernel": "step2_kernel (two FDTD steps per launch)",
             "algorithmic_bytes_per_cell_update": 60,
             "units_per_launch": "2 x interior cells (cell-updates)",
-            "limited_by": "vector-ALU issue (79-83 % VALU busy in the counter runs); the kernel moves 60 B per "
+            "limited_by": "the latency of a plane of the march (one block of 16 wavefronts per CU); the kernel moves 60 B per "
                           "two cell-updates, about 0.55x the one-step algorithmic bytes",
             "alu": {"achieved": tflops, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": tflops / FP32_PEAK_TFLOPS, "flop_per_cell_update": FLOP_PER_CELL_UPDATE,

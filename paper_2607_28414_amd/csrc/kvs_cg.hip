@@ -5,16 +5,20 @@
 //   non-finite inner products: Sec. 3.2.3),
 //   f_S,a = (F_a(-a) + 2 F_a + F_a(+a))/4 - (phi(+a) - phi(-a))/(2 h_a).
 //
-// One CG iteration is two fused HBM sweeps plus two one-block finalize
-// kernels, with every scalar (alpha, beta, r.r, the stop flag) kept on the
-// device, so the host only polls a flag once per chunk of iterations:
-//   sweep 1: p' = z + beta p (z = r, or r / diag(A) for Jacobi), A p' from
+// One CG iteration is two fused HBM sweeps, with every scalar (alpha, beta,
+// r.r, the stop flag) kept on the device, so the host only polls a flag once
+// per chunk of iterations:
+//   sweep 1: beta, the stop test and the iteration count from the sums before;
+//            p' = z + beta p (z = r, or r / diag(A) for Jacobi), A p' from
 //            the 7-point stencil, block partials of p'.Ap'
 //            (reads r, p; writes p': 24 B per cell)
-//   finalize: alpha = r.z / p.Ap with the breakdown guard
-//   sweep 2: A p' recomputed from p', phi += alpha p', r -= alpha Ap',
+//   sweep 2: alpha = r.z / p.Ap with the breakdown guard;
+//            A p' recomputed from p', phi += alpha p', r -= alpha Ap',
 //            partials of r.r and r.z (reads phi, p', r; writes phi, r: 40 B)
-//   finalize: beta, the stop test, the iteration count
+// The scalars are formed at the start of each sweep while the partials are
+// few, else by a one-block kernel between them (kvs_cg_scalars.hpp).  With
+// direction and residual in FP32 and no network two iterations share a pair of
+// sweeps instead (kvs_cg_pair.hip).
 // Recomputing A p' costs a few flops and saves storing and re-reading it.
 // Flexible PCG (learned preconditioner): the update writes the new residual
 // into a second buffer, and the network's output kernel, as it writes z, also

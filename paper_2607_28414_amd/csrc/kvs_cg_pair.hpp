@@ -1,5 +1,5 @@
 // Two CG iterations per pair of sweeps for FP32 storage of direction and
-// residual (kvs_cg_pair.hip), as the projection's driver launches them.
+// residual (kvs_cg_pair.hip), as the projection's host loop launches them.
 #pragma once
 
 #include "kvs_internal.hpp"
