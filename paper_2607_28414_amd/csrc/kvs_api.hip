@@ -652,7 +652,9 @@ kvs_status kvs_step(kvs_ctx* c, int64_t nsteps) {
             c->launch_ev[0] = ea;
             c->launch_ev[1] = eb;
         }
-        const hipError_t le = adv == 2 ? kvs_launch_step2(c, gn, gn1) : kvs_launch_step(c, gn);
+        const hipError_t le = adv == 2               ? kvs_launch_step2(c, gn, gn1)
+                              : kvs_step1_applies(c) ? kvs_launch_step1(c, gn)
+                                                     : kvs_launch_step(c, gn);
         c->launch_ev[0] = c->launch_ev[1] = nullptr;
         c->probe_fused_out = nullptr;
         c->probe_mid_out = nullptr;

@@ -305,6 +305,9 @@ hipError_t kvs_launch_force_pattern(kvs_ctx* c, const kvs_force_pattern* p);
 // One FDTD step from (u[cur], w[cur]) into (u[1-cur], w[1-cur]) with source
 // amplitude gn (0: no force read).  Returns the launch error.
 hipError_t kvs_launch_step(kvs_ctx* c, double gn);
+// the same step on the two-step kernel's march, where it is the faster one
+bool kvs_step1_applies(const kvs_ctx* c);
+hipError_t kvs_launch_step1(kvs_ctx* c, double gn);
 // two steps in one launch (kvs_step2.hip) with source amplitudes gn, gn2:
 // whether the layer, probes and grid allow it, and whether the context is one
 // of those that kvs_step_blocking_applies names
