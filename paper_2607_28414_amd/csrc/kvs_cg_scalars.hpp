@@ -54,9 +54,18 @@ __device__ __forceinline__ void cg_apply_beta(CgState& s, double rr, double rz) 
     cg_stop_test(s);
 }
 
+// Smallest r1.r1 / r.r a pair's second iteration is formed from.  r1.r1 and
+// p1.A p1 are differences of sums the size of r.r and p.q, with about 1e-15 of
+// those in rounding error: below 1e-15 / kPairFall they would have no digits.
+// On a grid of a few unknowns one iteration takes the residual to 0, and the
+// second one went along a direction of noise with a step of any size (3 x 3 x 3
+// nodes with Jacobi: phi off by half, KVS_ENOTCONV).  On ordinary grids r1.r1 /
+// r.r stays above 0.1 (20^3 to 60^3 nodes, 100 to 300 iterations).
+constexpr double kPairFall = 1e-6;
+
 // Two iterations at once (kvs_cg_pair.hip): the coefficients of the pair from
-// p.q, r.q, q.q, r.Ar, q.Ar, q.Aq; one iteration alone where it ends the solve
-// or the second has no positive p.Ap.
+// p.q, r.q, q.q, r.Ar, q.Ar, q.Aq; one iteration alone where it ends the solve,
+// the residual falls by more than kPairFall or the second has no positive p.Ap.
 __device__ __forceinline__ void cg_apply_pair(CgState& s, double pq, double rq, double qq, double rar, double qar,
                                               double qaq) {
     s.pAp = pq;
@@ -72,7 +81,7 @@ __device__ __forceinline__ void cg_apply_pair(CgState& s, double pq, double rq, 
     const double pap1 = zs * zs * (rar - 2.0 * a0 * qar + a0 * a0 * qaq) + 2.0 * zs * b0 * (rq - a0 * qq) + b0 * b0 * pq;
     const long long last = s.fixed_iters > 0 ? s.fixed_iters : s.max_iter;
     const bool met = s.fixed_iters <= 0 && !(sqrt(r11 / s.bb) >= sqrt(s.tol2));
-    const bool two = !met && s.iters + 1 < last && r11 > 0.0 && isfinite(r11) && pap1 > 0.0 && isfinite(pap1);
+    const bool two = !met && s.iters + 1 < last && r11 > kPairFall * s.rr && isfinite(r11) && pap1 > 0.0 && isfinite(pap1);
     s.alpha = a0;
     s.pair_a0 = a0;
     s.pair_b0 = two ? b0 : 0.0;
