@@ -549,10 +549,10 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
     const int S = LINE ? nx : N;                // nodes of a component in LDS
     T* su = reinterpret_cast<T*>(small_lds);    // [NB][3][S]
     T* sw = su + NB * 3 * S;                    // [NB][3][S]
-    T* senv = sw + NB * 3 * S;                  // [kSmallChunk]: the chunk's envelope values, and a 0
+    T* senv = sw + NB * 3 * S;                  // [kSmallChunk]: the chunk's envelope values; LINE: and a 0
     const long long pf = np > 0 ? probe_first[blockIdx.x] : 0;
     const int npi = np > 0 ? (int)(probe_first[blockIdx.x + 1] - pf) : 0;
-    T* strace = senv + kSmallChunk + 1;                                 // [kSmallChunk][npi]: probe values
+    T* strace = senv + kSmallChunk + (LINE ? 1 : 0);                    // [kSmallChunk][npi]: probe values
     int* sprobe = reinterpret_cast<int*>(strace + kSmallChunk * npi);  // this instance's probe cells
     const int row = LINE ? nx * (1 + ny) : 0;  // node 0 of the row kept
     for (int q = threadIdx.x; q < 3 * S; q += nthr) {
@@ -563,7 +563,7 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
             sw[h * 3 * S + q] = a.w[g];
         }
     }
-    if (threadIdx.x == 0) senv[kSmallChunk] = T(0);
+    if (LINE && threadIdx.x == 0) senv[kSmallChunk] = T(0);
     for (int p = threadIdx.x; p < npi; p += nthr) {
         const int q = (int)probes[2 * (pf + p) + 1];
         // off the row kept: a node of the Dirichlet layer, 0
@@ -655,7 +655,8 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
                         if constexpr (VISC) nw[(cb + c) * S + cell[m]] = wr[m][c];
                     }
             lds_barrier();  // the new state is complete
-            for (int p = threadIdx.x; p < npi; p += nthr) strace[sc * npi + p] = *(sprobe[p] >= 0 ? nu + sprobe[p] : senv + kSmallChunk);
+            for (int p = threadIdx.x; p < npi; p += nthr)
+                strace[sc * npi + p] = *(!LINE || sprobe[p] >= 0 ? nu + sprobe[p] : senv + kSmallChunk);
         }
         lds_barrier();  // the chunk's probe values are complete
         for (int r = threadIdx.x >> 6; r < cn; r += nthr >> 6)
@@ -687,13 +688,13 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
 
 // LDS of the persistent kernel: the state (6 N values), a chunk's envelope
 // and probe values, and the probe cells, for the instance with the most
-// probes.
+// probes.  (A line takes less: two copies of a ninth of that state, and a 0.)
 template <typename T>
 size_t small_lds_bytes(const kvs_batch* b, const kvs_ctx* c) {
     int64_t most = 0;
     for (size_t i = 0; i + 1 < b->probe_first.size(); ++i)
         most = std::max<int64_t>(most, b->probe_first[i + 1] - b->probe_first[i]);
-    return (6 * (size_t)c->N + kSmallChunk * (1 + (size_t)most) + 1) * sizeof(T) + sizeof(int) * (size_t)most;
+    return (6 * (size_t)c->N + kSmallChunk * (1 + (size_t)most)) * sizeof(T) + sizeof(int) * (size_t)most;
 }
 
 // Threads per workgroup (a multiple of 64, at most 1024, enough for one
