@@ -589,6 +589,22 @@ kvs_status kvs_set_step_blocking(kvs_ctx* ctx, int32_t steps);
  * and off the planes k = 0 and nz - 1; else 0 (FP64, lossless, wide and
  * peak-mapped contexts too, although kvs_step pairs their steps as well). */
 int32_t kvs_step_blocking_applies(const kvs_ctx* ctx);
+/* What kvs_step launched last: *kernel is a kvs_step_kernel, tile[0..2] the
+ * cells of its blocks in x and y and their z planes (host array of 3).  Either
+ * may be NULL. */
+typedef enum {
+    KVS_STEP_NONE = 0,  /* no step yet */
+    KVS_STEP_TILED = 1, /* one step per launch, one of the variants */
+    KVS_STEP_MARCH = 2, /* one step per launch, the two-step kernel's march (contexts with an absorbing layer) */
+    KVS_STEP_TWO = 3    /* two steps per launch */
+} kvs_step_kernel;
+kvs_status kvs_last_step_launch(const kvs_ctx* ctx, int32_t* kernel, int32_t* tile);
+/* Tile of two-step launches: 0: 128 x 8 cells, 1: 64 x 16, 2: 64 x 8,
+ * 3: 192 x 5; -1 (the default): the one whose blocks finish first by a model of
+ * the march; other values KVS_EINVAL.  Tiles that a context does not offer
+ * (FP64: all but 2; with peak planes 0 and 3; grids of two rows more than the
+ * tile) leave the choice to the model.  Every tile computes the same update. */
+kvs_status kvs_set_two_step_tile(kvs_ctx* ctx, int32_t tile);
 /* Time every variant on this context's grid, precision and medium, each with
  * the automatic z split and with 16-, 32- and 64-plane z segments
  * (trial_steps >= 1 launches each, after one untimed launch), and keep the

@@ -652,13 +652,16 @@ kvs_status kvs_step(kvs_ctx* c, int64_t nsteps) {
             c->launch_ev[0] = ea;
             c->launch_ev[1] = eb;
         }
-        const hipError_t le = adv == 2               ? kvs_launch_step2(c, gn, gn1)
-                              : kvs_step1_applies(c) ? kvs_launch_step1(c, gn)
-                                                     : kvs_launch_step(c, gn);
+        const bool march = adv == 1 && kvs_step1_applies(c);
+        const hipError_t le = adv == 2 ? kvs_launch_step2(c, gn, gn1)
+                              : march  ? kvs_launch_step1(c, gn)
+                                       : kvs_launch_step(c, gn);
         c->launch_ev[0] = c->launch_ev[1] = nullptr;
         c->probe_fused_out = nullptr;
         c->probe_mid_out = nullptr;
         API_HIP(c, le);
+        c->last_kernel = adv == 2 ? KVS_STEP_TWO : march ? KVS_STEP_MARCH : KVS_STEP_TILED;
+        std::copy_n(c->launched_tile, 3, c->last_tile);
         if (c->pml_cells > 0) API_HIP(c, kvs_launch_pml(c, gn));
         c->cur = 1 - c->cur;
         if (c->nprobes > 0) c->trace_steps += adv;  // last slot filled by the next launch or the gather below
@@ -1125,6 +1128,20 @@ kvs_status kvs_set_step_blocking(kvs_ctx* c, int32_t steps) {
     if (!c) return KVS_EINVAL;
     if (steps != 1 && steps != 2) return fail(c, KVS_EINVAL, "steps per launch must be 1 or 2");
     c->step_block = steps;
+    return KVS_OK;
+}
+
+kvs_status kvs_set_two_step_tile(kvs_ctx* c, int32_t tile) {
+    if (!c) return KVS_EINVAL;
+    if (tile < -1 || tile > 3) return fail(c, KVS_EINVAL, "two-step tile must be -1..3");
+    c->step2_tile = tile;
+    return KVS_OK;
+}
+
+kvs_status kvs_last_step_launch(const kvs_ctx* c, int32_t* kernel, int32_t* tile) {
+    if (!c) return KVS_EINVAL;
+    if (kernel) *kernel = c->last_kernel;
+    if (tile) std::copy_n(c->last_tile, 3, tile);
     return KVS_OK;
 }
 

@@ -170,6 +170,12 @@ struct kvs_ctx {
     int step_remap = 1;
     // steps per launch where the two-step kernel applies (1 or 2)
     int step_block = 2;
+    int step2_tile = -1;  // tile shape of two-step launches where it is offered (-1: by the model of the march)
+    // kvs_step's last launch: kvs_step_kernel and its tile (cells in x and y, z
+    // planes per block); launched_tile: of any step launch, trials included
+    int last_kernel = KVS_STEP_NONE;
+    int last_tile[3] = {0, 0, 0};
+    int launched_tile[3] = {0, 0, 0};
     // storage of the projection's CG search direction (KVS_FP64 or KVS_FP32;
     // set to the state precision at creation); p_dirty: both direction
     // buffers are cleared before the next solve (after a change, the other

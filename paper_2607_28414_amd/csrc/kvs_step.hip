@@ -40,6 +40,9 @@ hipError_t launch_shape(kvs_ctx* c, StepArgs<T> a) {
     a.kchunk = c->step_zchunk > 0 ? std::min(c->step_zchunk, a.nz - 2) : choose_kchunk(a.gx * a.gy, a.nz - 2, cap);
     a.gz = (a.nz - 2 + a.kchunk - 1) / a.kchunk;
     a.pblocks = a.pout ? (int)((a.np + 64 * WX * BY - 1) / (64 * WX * BY)) : 0;
+    c->launched_tile[0] = 64 * WX * VEC;
+    c->launched_tile[1] = BY;
+    c->launched_tile[2] = a.kchunk;
     const int blocks = a.gx * a.gy * a.gz + a.pblocks;
     if (c->launch_ev[0])
         hipExtLaunchKernelGGL(kern, dim3(blocks), dim3(64 * WX, BY), 0, c->stream, c->launch_ev[0],

@@ -204,6 +204,9 @@ hipError_t launch(kvs_ctx* c, StepArgs<float> a) {
     a.kchunk = choose_kchunk(a.gx * a.gy, a.nz - 2, cap);
     a.gz = (a.nz - 2 + a.kchunk - 1) / a.kchunk;
     a.pblocks = a.pout ? (int)((a.np + 64 * WX * R - 1) / (64 * WX * R)) : 0;
+    c->launched_tile[0] = 64 * WX;
+    c->launched_tile[1] = R;
+    c->launched_tile[2] = a.kchunk;
     const int blocks = a.gx * a.gy * a.gz + a.pblocks;
     if (c->launch_ev[0])
         hipExtLaunchKernelGGL(kern, dim3(blocks), dim3(64 * WX, R), 0, c->stream, c->launch_ev[0], c->launch_ev[1], 0, a);

@@ -35,8 +35,9 @@ struct Step2Plan {
     int shape = -1, gx = 1, gy = 1, kchunk = 1;
 };
 
-void consider(Step2Plan& best, int shape, const kvs_grid& g, int cap, int zchunk) {
-    if (!step2_offers(shape, g.ny)) return;
+// only: the shape asked for, where the context offers it, else -1
+void consider(Step2Plan& best, int shape, int only, const kvs_grid& g, int cap, int zchunk) {
+    if (!step2_offers(shape, g.ny) || (only >= 0 && shape != only)) return;
     const int planes = (int)g.nz - 2;
     const int gx = overlap_tiles((int)g.nx, 64 * kStep2Wx[shape]), gy = overlap_tiles((int)g.ny, kStep2Rows[shape]);
     const double units = step2_units(shape);
@@ -61,6 +62,9 @@ hipError_t launch_shape(kvs_ctx* c, Step2Args<T>& A2, const Step2Peaks<T>& pk) {
     auto kern = step2_kernel<T, HET, VISC, FORCE, PEAK, WX, R>;
     a.gz = (a.nz - 2 + a.kchunk - 1) / a.kchunk;
     a.pblocks = a.np > 0 && (a.pout || A2.pmid) ? (int)((a.np + 64 * WX * R - 1) / (64 * WX * R)) : 0;
+    c->launched_tile[0] = 64 * WX;
+    c->launched_tile[1] = R;
+    c->launched_tile[2] = a.kchunk;
     const int blocks = a.gx * a.gy * a.gz + a.pblocks;
     if (c->launch_ev[0])
         hipExtLaunchKernelGGL(kern, dim3(blocks), dim3(64 * WX, R), 0, c->stream, c->launch_ev[0], c->launch_ev[1], 0,
@@ -81,12 +85,15 @@ template <typename T, bool HET, bool VISC, bool FORCE>
 hipError_t launch_medium(kvs_ctx* c, Step2Args<T>& A2, const Step2Peaks<T>& pk) {
     const kvs_grid& g = c->grid;
     Step2Plan p;
+    const int want = c->step2_tile;
+    const bool has = sizeof(T) == 8 ? want == 2 : want >= 0 && (pk.n == 0 || want == 1 || want == 2);
+    const int only = has && step2_offers(want, g.ny) ? want : -1;
     // peak maps: the shape that fits most row lengths (FP32: 64 x 16), compiled
     // for them alone; 64 x 8 where the grid's rows rule that out
     if constexpr (sizeof(T) == 4) {
-        if (pk.n > 0) consider(p, 1, g, shape_cap<T, HET, VISC, FORCE, 1>(), c->step2_zchunk);
+        if (pk.n > 0) consider(p, 1, only, g, shape_cap<T, HET, VISC, FORCE, 1>(), c->step2_zchunk);
     }
-    if (pk.n > 0 && p.shape < 0) consider(p, 2, g, shape_cap<T, HET, VISC, FORCE, 2>(), c->step2_zchunk);
+    if (pk.n > 0 && p.shape < 0) consider(p, 2, only, g, shape_cap<T, HET, VISC, FORCE, 2>(), c->step2_zchunk);
     if (p.shape >= 0) {
         A2.a.gx = p.gx;
         A2.a.gy = p.gy;
@@ -97,11 +104,11 @@ hipError_t launch_medium(kvs_ctx* c, Step2Args<T>& A2, const Step2Peaks<T>& pk) 
         return launch_shape<T, HET, VISC, FORCE, 2, true>(c, A2, pk);
     }
     if constexpr (sizeof(T) == 4) {
-        consider(p, 0, g, shape_cap<T, HET, VISC, FORCE, 0>(), c->step2_zchunk);
-        consider(p, 1, g, shape_cap<T, HET, VISC, FORCE, 1>(), c->step2_zchunk);
-        consider(p, 3, g, shape_cap<T, HET, VISC, FORCE, 3>(), c->step2_zchunk);
+        consider(p, 0, only, g, shape_cap<T, HET, VISC, FORCE, 0>(), c->step2_zchunk);
+        consider(p, 1, only, g, shape_cap<T, HET, VISC, FORCE, 1>(), c->step2_zchunk);
+        consider(p, 3, only, g, shape_cap<T, HET, VISC, FORCE, 3>(), c->step2_zchunk);
     }
-    consider(p, 2, g, shape_cap<T, HET, VISC, FORCE, 2>(), c->step2_zchunk);
+    consider(p, 2, only, g, shape_cap<T, HET, VISC, FORCE, 2>(), c->step2_zchunk);
     A2.a.gx = p.gx;
     A2.a.gy = p.gy;
     A2.a.kchunk = p.kchunk;

@@ -18,6 +18,7 @@ LIB_PATH = os.path.join(PKG, "libkvs.so")
 KVS_OK, KVS_EINVAL, KVS_ENOMEM, KVS_EDEVICE, KVS_ENOTCONV, KVS_EBREAKDOWN, KVS_EUNSTABLE, KVS_ESTATE = range(8)
 KVS_FP64, KVS_FP32 = 0, 1
 KVS_PC_NONE, KVS_PC_JACOBI, KVS_PC_UNET = 0, 1, 2
+KVS_STEP_NONE, KVS_STEP_TILED, KVS_STEP_MARCH, KVS_STEP_TWO = 0, 1, 2, 3
 KVS_ARF_PLANE, KVS_ARF_POYNTING = 1, 2
 STATUS_NAMES = {0: "KVS_OK", 1: "KVS_EINVAL", 2: "KVS_ENOMEM", 3: "KVS_EDEVICE", 4: "KVS_ENOTCONV",
                 5: "KVS_EBREAKDOWN", 6: "KVS_EUNSTABLE", 7: "KVS_ESTATE"}
@@ -193,6 +194,8 @@ SIGNATURES = {
     "kvs_set_step_tuning": ([_P, C.c_int32, C.c_int32, C.c_int32], C.c_int),
     "kvs_autotune_step": ([_P, C.c_int32, C.POINTER(C.c_int32), _D, C.c_int32], C.c_int),
     "kvs_set_step_blocking": ([_P, C.c_int32], C.c_int),
+    "kvs_set_two_step_tile": ([_P, C.c_int32], C.c_int),
+    "kvs_last_step_launch": ([_P, C.POINTER(C.c_int32), C.POINTER(C.c_int32)], C.c_int),
     "kvs_set_direction_precision": ([_P, C.c_int32], C.c_int),
     "kvs_set_residual_precision": ([_P, C.c_int32], C.c_int),
     "kvs_kernel_time_split": ([_P, _D, C.POINTER(C.c_int64)], C.c_int),
@@ -554,6 +557,18 @@ def kvs_set_step_tuning(ctx, v, zchunk=0, remap=True):
 
 def kvs_set_step_blocking(ctx, steps):
     _check(lib().kvs_set_step_blocking(ctx, int(steps)), ctx)
+
+
+def kvs_set_two_step_tile(ctx, tile):
+    """Tile of two-step launches: 0 128x8, 1 64x16, 2 64x8, 3 192x5, -1 automatic."""
+    _check(lib().kvs_set_two_step_tile(ctx, int(tile)), ctx)
+
+
+def kvs_last_step_launch(ctx):
+    """(kernel, (cells in x, in y, z planes per block)) of kvs_step's last launch."""
+    kernel, tile = C.c_int32(), (C.c_int32 * 3)()
+    _check(lib().kvs_last_step_launch(ctx, C.byref(kernel), tile), ctx)
+    return kernel.value, tuple(tile)
 
 
 def kvs_set_direction_precision(ctx, precision):
