@@ -566,7 +566,9 @@ kvs_status kvs_unet_conv_check(int32_t ci, int32_t co, int32_t dil, const uint16
  * wavefronts per x row). */
 int32_t kvs_num_step_variants(void);
 /* Use variant v (0 <= v < kvs_num_step_variants()) for kvs_step.  Every
- * variant computes the same update; they differ in tile shape only. */
+ * variant computes the same update; they differ in tile shape only.  A variant
+ * other than 0, or a z split, also keeps the tiled kernel where the march would
+ * step a context with an absorbing layer. */
 kvs_status kvs_set_step_variant(kvs_ctx* ctx, int32_t v);
 /* Full step-kernel tuning: variant v, z planes per block zchunk (0 = split
  * z so that the blocks fill whole rounds of resident blocks), remap != 0
@@ -608,8 +610,13 @@ kvs_status kvs_set_two_step_tile(kvs_ctx* ctx, int32_t tile);
 /* Time every variant on this context's grid, precision and medium, each with
  * the automatic z split and with 16-, 32- and 64-plane z segments
  * (trial_steps >= 1 launches each, after one untimed launch), and keep the
- * fastest.  ms_per_launch[v] is the best z split's time for variant v.  The state is not advanced: trial launches only write the
- * buffers the next real step overwrites.  Needs material and dt.  chosen and
+ * fastest for the one-step launches.  Steps that kvs_step takes in pairs do not
+ * use it: there it decides the odd last step only.  In a context with an
+ * absorbing layer whose steps the two-step kernel's march can take one at a time
+ * (FP32, nx <= 257) the march is timed too, and steps them unless a variant was
+ * faster.  ms_per_launch[v] is the best z split's time for variant v.  The state
+ * is not advanced: trial launches only write the buffers the next real step
+ * overwrites.  Needs material and dt.  chosen (the fastest variant) and
  * ms_per_launch (cap entries, one per variant) may be NULL. */
 kvs_status kvs_autotune_step(kvs_ctx* ctx, int32_t trial_steps, int32_t* chosen, double* ms_per_launch,
                              int32_t cap);

@@ -1111,6 +1111,7 @@ kvs_status kvs_set_step_variant(kvs_ctx* c, int32_t v) {
     if (!c) return KVS_EINVAL;
     if (v < 0 || v >= kvs_step_variant_count()) return fail(c, KVS_EINVAL, "no such step variant");
     c->step_variant = v;
+    c->step1_off = v != 0 || c->step_zchunk != 0;
     return KVS_OK;
 }
 
@@ -1121,6 +1122,7 @@ kvs_status kvs_set_step_tuning(kvs_ctx* c, int32_t v, int32_t zchunk, int32_t re
     c->step_variant = v;
     c->step_zchunk = c->step2_zchunk = zchunk;
     c->step_remap = remap != 0;
+    c->step1_off = v != 0 || zchunk != 0;
     return KVS_OK;
 }
 
@@ -1177,26 +1179,34 @@ kvs_status kvs_autotune_step(kvs_ctx* c, int32_t trial_steps, int32_t* chosen, d
     int best = 0, best_z = 0;
     double best_ms = 1e300;
     const int saved_z = c->step_zchunk;
+    // ms per launch of variant v (-1: the one-step march): a warm-up launch, then
+    // timed launches; cur is not flipped, so every launch recomputes the same
+    // next state from the same current state
+    auto trial = [&](int v, double* per) {
+        auto launch = [&]() { return v < 0 ? kvs_launch_step1(c, 0.0) : kvs_launch_step_variant(c, 0.0, v); };
+        hipError_t e = launch();
+        if (e == hipSuccess) e = hipEventRecord(e0, c->stream);
+        for (int q = 0; q < trial_steps && e == hipSuccess; ++q) e = launch();
+        if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
+        if (e == hipSuccess) e = hipEventSynchronize(e1);
+        float ms = 0.f;
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        *per = ms / trial_steps;
+        return e;
+    };
+    auto failed = [&](hipError_t e) {
+        c->step_zchunk = saved_z;
+        (void)hipEventDestroy(e0);
+        (void)hipEventDestroy(e1);
+        return fail(c, KVS_EDEVICE, std::string("autotune: ") + hipGetErrorString(e));
+    };
     for (int v = 0; v < nv; ++v) {
         double v_best = 1e300;
         for (int zi = 0; zi < 4; ++zi) {
             c->step_zchunk = zchunks[zi];
-            // warm-up launch, then timed launches; cur is not flipped, so every
-            // launch recomputes the same next state from the same current state
-            hipError_t e = kvs_launch_step_variant(c, 0.0, v);
-            if (e == hipSuccess) e = hipEventRecord(e0, c->stream);
-            for (int q = 0; q < trial_steps && e == hipSuccess; ++q) e = kvs_launch_step_variant(c, 0.0, v);
-            if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
-            if (e == hipSuccess) e = hipEventSynchronize(e1);
-            float ms = 0.f;
-            if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-            if (e != hipSuccess) {
-                c->step_zchunk = saved_z;
-                (void)hipEventDestroy(e0);
-                (void)hipEventDestroy(e1);
-                return fail(c, KVS_EDEVICE, std::string("autotune: ") + hipGetErrorString(e));
-            }
-            const double per = ms / trial_steps;
+            double per = 0.0;
+            const hipError_t e = trial(v, &per);
+            if (e != hipSuccess) return failed(e);
             v_best = std::min(v_best, per);
             if (per < best_ms) {
                 best_ms = per;
@@ -1206,10 +1216,19 @@ kvs_status kvs_autotune_step(kvs_ctx* c, int32_t trial_steps, int32_t* chosen, d
         }
         if (ms_per_launch && v < cap) ms_per_launch[v] = v_best;
     }
+    // the march takes the step of contexts with a layer unless a variant beat it
+    bool march_off = false;
+    if (kvs_step1_offered(c)) {
+        double per = 0.0;
+        const hipError_t e = trial(-1, &per);
+        if (e != hipSuccess) return failed(e);
+        march_off = best_ms < per;
+    }
     c->step_zchunk = best_z;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     c->step_variant = best;
+    c->step1_off = march_off;
     if (chosen) *chosen = best;
     return KVS_OK;
 }

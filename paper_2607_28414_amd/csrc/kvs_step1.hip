@@ -234,13 +234,14 @@ hipError_t launch_force(kvs_ctx* c, const StepArgs<float>& a) {
 
 }  // namespace
 
-bool kvs_step1_applies(const kvs_ctx* c) {
+bool kvs_step1_offered(const kvs_ctx* c) {
     // rows of one tile: 320 x 200 x 200 in two of 256 took 366 us against 333 of
-    // the tiled kernel.  Default tuning only: a variant or z split that the
-    // caller chose is kept.  Byte offsets within a plane are 32-bit.
-    return c->grid.nx <= 257 && c->pml_cells > 0 && c->prec == KVS_FP32 && c->step_variant == 0 && c->step_zchunk == 0 &&
-           c->N < ((int64_t)1 << 31) && c->grid.nx * c->grid.ny < ((int64_t)1 << 30) - 1024;
+    // the tiled kernel.  Byte offsets within a plane are 32-bit.
+    return c->grid.nx <= 257 && c->pml_cells > 0 && c->prec == KVS_FP32 && c->N < ((int64_t)1 << 31) &&
+           c->grid.nx * c->grid.ny < ((int64_t)1 << 30) - 1024;
 }
+
+bool kvs_step1_applies(const kvs_ctx* c) { return kvs_step1_offered(c) && !c->step1_off; }
 
 hipError_t kvs_launch_step1(kvs_ctx* c, double gn) {
     const kvs_grid& g = c->grid;
