@@ -352,37 +352,82 @@ int step2_shape(const kvs_grid& g) {
     return best;
 }
 
+// What the launches of a pair of steps take, us: the tile shapes follow one
+// another, each with a start (code, arguments, first planes) and its span of
+// planes.  Fitted to 360 ragged batches of 1 to 40 instances with the instances
+// in one shape, 7 % rms.
+constexpr double kStep2StartUs[kStep2Shapes] = {3.0, 1.0, 6.0, 3.0}, kStep2PlaneUs[kStep2Shapes] = {1.4, 1.7, 0.75, 1.2};
+
+// The work list of the two-step launches: instances by tile shape, per shape
+// the segment length whose launch ends first.  Measured, us per step, 24
+// instances of edges 64 to 160: segments of 64 planes in XCD-contiguous order
+// 375, 32 planes in this order 320; 64 instances of edges 96 to 192: 1521, and
+// 1455 with 96 planes.
+//
+// Each instance takes the shape with the least work (step2_shape), or all of
+// them one shape where by the model that ends by a fifth earlier: small
+// instances in several shapes are several short launches, one after the other.
+// us per step, each its own shape and all 64 x 8: lossless with force on every
+// step, 28 x 79 x 6 and 105 x 11 x 7 13.2 and 7; three instances of up to
+// 80 000 cells 20.2 and 6.4; 12 of up to 10^6 cells 27.8 and 7.8.  Above
+// kStep2MergeUs launches are long enough to hide it (24 instances of edges 64 to
+// 160: 600 us, one shape).
+constexpr double kStep2MergeUs = 200.0;
+
+void step2_plan_work(kvs_batch* b, std::vector<int4>& work) {
+    struct Part {
+        int shape, most;
+        std::vector<int> members;
+        Step2List list;
+    };
+    const int n = (int)b->inst.size();
+    auto plan = [&](int only, double* us) {
+        std::vector<Part> parts;
+        *us = 0.0;
+        for (int sh = 0; sh < kStep2Shapes; ++sh) {
+            Part p{sh, 0, {}, {}};
+            for (int i = 0; i < n; ++i) {
+                const kvs_grid& g = b->inst[(size_t)i]->grid;
+                if ((only >= 0 && step2_offers(only, g.ny) ? only : step2_shape(g)) == sh) p.members.push_back(i);
+            }
+            if (p.members.empty()) continue;
+            for (int m : {8, 12, 16, 24, 32, 48, 64, 96, 128}) {
+                Step2List l = step2_list(b, p.members, sh, m);
+                if (p.most == 0 || l.span < p.list.span) {
+                    p.list = std::move(l);
+                    p.most = m;
+                }
+            }
+            *us += kStep2StartUs[sh] + kStep2PlaneUs[sh] * (double)p.list.span;
+            parts.push_back(std::move(p));
+        }
+        return parts;
+    };
+    double own = 0.0;
+    std::vector<Part> best = plan(-1, &own);
+    double least = 0.8 * own;
+    for (int only = 0; own < kStep2MergeUs && only < kStep2Shapes; ++only) {
+        double us = 0.0;
+        std::vector<Part> p = plan(only, &us);
+        if (us >= least) continue;
+        best = std::move(p);
+        least = us;
+    }
+    b->groups2.clear();
+    b->chunk2.assign((size_t)n, 1);
+    for (const Part& p : best) {
+        for (int i : p.members) b->chunk2[(size_t)i] = step2_chunk(b->inst[(size_t)i]->grid.nz, p.most);
+        b->groups2.push_back({p.shape, (int)work.size(), (int)p.list.order.size()});
+        work.insert(work.end(), p.list.order.begin(), p.list.order.end());
+    }
+}
+
 hipError_t prepare2(kvs_batch* b) {
     b->two_ok = kvs_batch_step2_supported(b);
     if (!b->two_ok) return hipSuccess;
     const int n = (int)b->inst.size();
     std::vector<int4> work;
-    if (!b->dev_work2) {
-        // per tile shape the segment length whose launch ends first.  Measured,
-        // us per step, 24 instances of edges 64 to 160: segments of 64 planes in
-        // XCD-contiguous order 375, 32 planes in this order 320; 64 instances
-        // of edges 96 to 192: 1521, and 1455 with 96 planes
-        b->groups2.clear();
-        b->chunk2.assign((size_t)n, 1);
-        for (int sh = 0; sh < kStep2Shapes; ++sh) {
-            std::vector<int> members;
-            for (int i = 0; i < n; ++i)
-                if (step2_shape(b->inst[(size_t)i]->grid) == sh) members.push_back(i);
-            if (members.empty()) continue;
-            Step2List best;
-            int most = 0;
-            for (int m : {8, 12, 16, 24, 32, 48, 64, 96, 128}) {
-                Step2List l = step2_list(b, members, sh, m);
-                if (most == 0 || l.span < best.span) {
-                    best = std::move(l);
-                    most = m;
-                }
-            }
-            for (int i : members) b->chunk2[(size_t)i] = step2_chunk(b->inst[(size_t)i]->grid.nz, most);
-            b->groups2.push_back({sh, (int)work.size(), (int)best.order.size()});
-            work.insert(work.end(), best.order.begin(), best.order.end());
-        }
-    }
+    if (!b->dev_work2) step2_plan_work(b, work);
     std::vector<BatchInst2> params((size_t)n);
     const double* env = reinterpret_cast<const double*>(static_cast<const char*>(b->dev_params) +
                                                         sizeof(BatchInst<float>) * (size_t)n);
