@@ -1346,8 +1346,8 @@ kvs_status kvs_batch_share_projection(kvs_batch* b, int32_t src, int32_t dst) {
 }
 
 // Probe tables of the two-step launches, for every instance with probes: one
-// entry per 64-cell segment of each grid row (the row's offset into the probe
-// table where that segment holds a probe, else -1), and per probed row nx
+// entry per grid row (the row's offset into the probe table where it holds a
+// probe, else -1), and per probed row nx
 // instance-local probe indices.  Probe cells must be distinct and off the
 // planes k = 0, nz - 1 (else two-step launches are not used).
 static kvs_status batch_upload_probes2(kvs_batch* b) {
@@ -1506,7 +1506,7 @@ kvs_status kvs_batch_step(kvs_batch* b, int64_t nsteps) {
         b->trace_cap = cap;
         b->graph_valid = false;
     }
-    BATCH_HIP(b, kvs_batch_prepare(b));
+    BATCH_HIP(b, kvs_batch_prepare(b, nsteps));
     int64_t flips = 0;
     BATCH_HIP(b, kvs_batch_run(b, nsteps, &flips));
     for (kvs_ctx* c : b->inst) {
@@ -1585,7 +1585,7 @@ kvs_status kvs_batch_autotune(kvs_batch* b, int32_t trial_steps, int32_t* varian
             b->variant = v;
             b->zchunk = zs[zi];
             batch_retile(b);
-            e = kvs_batch_prepare(b);
+            e = kvs_batch_prepare(b, 1);  // trials are one-step launches
             if (e == hipSuccess) e = kvs_batch_trial_launch(b);
             if (e == hipSuccess) e = hipEventRecord(e0, b->stream);
             for (int q = 0; q < trial_steps && e == hipSuccess; ++q) e = kvs_batch_trial_launch(b);

@@ -126,11 +126,11 @@ __global__ void batch_probe_kernel(const BatchInst<T>* inst, const long long* pr
     }
 }
 
+// The instances' parameter table and envelopes, staged in `host` (kept by the
+// caller until the stream has copied it), and the work list.
 template <typename T>
-hipError_t prepare_t(kvs_batch* b) {
+hipError_t prepare_t(kvs_batch* b, std::vector<char>& host, std::vector<int4>& work) {
     const int n = (int)b->inst.size();
-    std::vector<BatchInst<T>> params((size_t)n);
-    std::vector<int4> work;
     bool visc = false;
     size_t env_total = 0;
     for (int i = 0; i < n; ++i) env_total += b->inst[(size_t)i]->env.size();
@@ -146,7 +146,9 @@ hipError_t prepare_t(kvs_batch* b) {
         b->graph_valid = false;  // the graph holds the old table's address
     }
     double* env_dev = reinterpret_cast<double*>(static_cast<char*>(b->dev_params) + pbytes);
-    std::vector<double> env_host(std::max<size_t>(env_total, 1), 0.0);
+    host.assign(pbytes + ebytes, 0);
+    BatchInst<T>* const params = reinterpret_cast<BatchInst<T>*>(host.data());
+    double* const env_host = reinterpret_cast<double*>(host.data() + pbytes);
     size_t off = 0;
     std::vector<int> shape((size_t)n);
     for (int i = 0; i < n; ++i) {
@@ -154,11 +156,11 @@ hipError_t prepare_t(kvs_batch* b) {
         shape[(size_t)i] = instance_shape(b, c);
         int by = 0, vec = 0, wx = 0;
         batch_shape_dims(shape[(size_t)i], &by, &vec, &wx);
-        params[(size_t)i].a[0] = instance_args<T>(c, c->cur, by, vec, wx, b->zchunk);
-        params[(size_t)i].a[1] = instance_args<T>(c, 1 - c->cur, by, vec, wx, b->zchunk);
-        params[(size_t)i].env = env_dev + off;
-        params[(size_t)i].n_env = (long long)c->env.size();
-        std::copy(c->env.begin(), c->env.end(), env_host.begin() + off);
+        params[i].a[0] = instance_args<T>(c, c->cur, by, vec, wx, b->zchunk);
+        params[i].a[1] = instance_args<T>(c, 1 - c->cur, by, vec, wx, b->zchunk);
+        params[i].env = env_dev + off;
+        params[i].n_env = (long long)c->env.size();
+        std::copy(c->env.begin(), c->env.end(), env_host + off);
         off += c->env.size();
         visc = visc || c->viscous;
     }
@@ -169,7 +171,7 @@ hipError_t prepare_t(kvs_batch* b) {
             const int first = (int)work.size();
             for (int i = 0; i < n; ++i) {
                 if (shape[(size_t)i] != sh) continue;
-                const StepArgs<T>& a = params[(size_t)i].a[0];
+                const StepArgs<T>& a = params[i].a[0];
                 for (int bz = 0; bz < a.gz; ++bz)
                     for (int by = 0; by < a.gy; ++by)
                         for (int bx = 0; bx < a.gx; ++bx) work.push_back(make_int4(i, bx, by, bz));
@@ -177,8 +179,7 @@ hipError_t prepare_t(kvs_batch* b) {
             if ((int)work.size() > first) b->groups.push_back({sh, first, (int)work.size() - first});
         }
     }
-    e = hipMemcpyAsync(b->dev_params, params.data(), pbytes, hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(env_dev, env_host.data(), ebytes, hipMemcpyHostToDevice, b->stream);
+    e = hipMemcpyAsync(b->dev_params, host.data(), pbytes + ebytes, hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess && !b->dev_work) {
         e = b->mem.get(&b->dev_work, sizeof(int4) * work.size());
         if (e == hipSuccess)
@@ -186,7 +187,6 @@ hipError_t prepare_t(kvs_batch* b) {
                                b->stream);
         b->nwork = (int)work.size();
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (visc != b->viscous) b->graph_valid = false;
     b->viscous = visc;
     return e;
@@ -422,13 +422,11 @@ void step2_plan_work(kvs_batch* b, std::vector<int4>& work) {
     }
 }
 
-hipError_t prepare2(kvs_batch* b) {
-    b->two_ok = kvs_batch_step2_supported(b);
-    if (!b->two_ok) return hipSuccess;
+// The two-step launches' parameter table and work list, staged as above.
+hipError_t prepare2(kvs_batch* b, std::vector<BatchInst2>& params, std::vector<int4>& work) {
     const int n = (int)b->inst.size();
-    std::vector<int4> work;
     if (!b->dev_work2) step2_plan_work(b, work);
-    std::vector<BatchInst2> params((size_t)n);
+    params.resize((size_t)n);
     const double* env = reinterpret_cast<const double*>(static_cast<const char*>(b->dev_params) +
                                                         sizeof(BatchInst<float>) * (size_t)n);
     for (int i = 0; i < n; ++i) {
@@ -466,7 +464,6 @@ hipError_t prepare2(kvs_batch* b) {
                                b->stream);
         b->nwork2 = (int)work.size();
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     return e;
 }
 
@@ -600,12 +597,16 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
     T* strace = senv + kSmallChunk + (LINE ? 1 : 0);                    // [kSmallChunk][npi]: probe values
     int* sprobe = reinterpret_cast<int*>(strace + kSmallChunk * npi);  // this instance's probe cells
     const int row = LINE ? nx * (1 + ny) : 0;  // node 0 of the row kept
-    for (int q = threadIdx.x; q < 3 * S; q += nthr) {
-        const int c = q / S, g = c * N + row + q % S;
-#pragma unroll
-        for (int h = 0; h < NB; ++h) {
-            su[h * 3 * S + q] = a.u[g];
-            sw[h * 3 * S + q] = a.w[g];
+    if constexpr (LINE) {
+        for (int c = 0; c < 3; ++c)
+            for (int i = threadIdx.x; i < S; i += nthr) {
+                su[c * S + i] = su[(3 + c) * S + i] = a.u[c * N + row + i];
+                sw[c * S + i] = sw[(3 + c) * S + i] = a.w[c * N + row + i];
+            }
+    } else {
+        for (int q = threadIdx.x; q < 3 * N; q += nthr) {
+            su[q] = a.u[q];
+            sw[q] = a.w[q];
         }
     }
     if (LINE && threadIdx.x == 0) senv[kSmallChunk] = T(0);
@@ -710,25 +711,39 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
         // the next chunk writes senv and strace only after the barrier that
         // follows its envelope load, i.e. after these reads
     }
-    // the run leaves the instance's state in the buffers current after nsteps:
-    // the cells from the registers, the Dirichlet layer as it was
+    // the run leaves the instance's state in the buffers current after nsteps
     T* du = (nsteps & 1) ? a.un : const_cast<T*>(a.u);
     T* dw = (nsteps & 1) ? a.wn : const_cast<T*>(a.w);
-    if (nsteps & 1)
+    if constexpr (LINE) {
+        // the cells from the registers, the Dirichlet layer as it was
+        if (nsteps & 1)
+            for (int c = 0; c < 3; ++c)
+                for (int g = threadIdx.x; g < N; g += nthr) {
+                    if (g >= row + 1 && g <= row + nx - 2) continue;
+                    du[c * N + g] = a.u[c * N + g];
+                    dw[c * N + g] = a.w[c * N + g];
+                }
+#pragma unroll
+        for (int m = 0; m < CPT; ++m)
+            if (cell[m] >= 0)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    du[(cb + c) * a.N + row + cell[m]] = ur[m][c];
+                    dw[(cb + c) * a.N + row + cell[m]] = wr[m][c];
+                }
+    } else {
+        // w in LDS is stale without viscosity: the registers hold it
+#pragma unroll
+        for (int m = 0; m < CPT; ++m)
+            if (cell[m] >= 0)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) sw[(cb + c) * N + cell[m]] = wr[m][c];
+        lds_barrier();
         for (int q = threadIdx.x; q < 3 * N; q += nthr) {
-            const int n = q % N, i = n % nx, j = (n / nx) % ny, k = n / (nx * ny);
-            if (i >= 1 && i <= nx - 2 && j >= 1 && j <= ny - 2 && k >= 1 && k <= nz - 2) continue;
-            du[q] = a.u[q];
-            dw[q] = a.w[q];
+            du[q] = su[q];
+            dw[q] = sw[q];
         }
-#pragma unroll
-    for (int m = 0; m < CPT; ++m)
-        if (cell[m] >= 0)
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                du[(cb + c) * a.N + row + cell[m]] = ur[m][c];
-                dw[(cb + c) * a.N + row + cell[m]] = wr[m][c];
-            }
+    }
 }
 
 // LDS of the persistent kernel: the state (6 N values), a chunk's envelope
@@ -846,10 +861,17 @@ bool kvs_batch_two_step_supported(const kvs_batch* b) {
     return visc;
 }
 
-hipError_t kvs_batch_prepare(kvs_batch* b) {
-    hipError_t e = b->prec == KVS_FP32 ? prepare_t<float>(b) : prepare_t<double>(b);
-    if (e == hipSuccess) e = prepare2(b);
-    return e;
+hipError_t kvs_batch_prepare(kvs_batch* b, int64_t nsteps) {
+    std::vector<char> host;
+    std::vector<BatchInst2> params2;
+    std::vector<int4> work, work2;
+    hipError_t e = b->prec == KVS_FP32 ? prepare_t<float>(b, host, work) : prepare_t<double>(b, host, work);
+    // tables of two-step launches only for a run that has some: made and copied
+    // for every run of a persistent batch too, they took 10 to 25 of its 50 to 80 us
+    b->two_ok = nsteps > 1 && b->step_block == 2 && !kvs_batch_small_path(b) && kvs_batch_step2_supported(b);
+    if (e == hipSuccess && b->two_ok) e = prepare2(b, params2, work2);
+    const hipError_t s = hipStreamSynchronize(b->stream);  // the staging vectors end here
+    return e != hipSuccess ? e : s;
 }
 
 hipError_t kvs_batch_run(kvs_batch* b, int64_t nsteps, int64_t* flips) {

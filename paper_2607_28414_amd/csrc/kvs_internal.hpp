@@ -288,9 +288,9 @@ struct kvs_batch {
     int64_t graph_start = -1, graph_steps = 0, graph_trace0 = -1;
     std::vector<uint8_t> graph_force;  // the per-step launch plan (see kvs_batch_run)
 
-    // two steps per launch: requested (1 or 2), and whether the batch allows
-    // it (set by kvs_batch_prepare: FP32, probe cells distinct and off the
-    // planes k = 0, nz - 1); the instances' two-step arguments [parity], the
+    // two steps per launch: requested (1 or 2), and whether the run has any
+    // (set by kvs_batch_prepare: FP32, probe cells distinct and off the planes
+    // k = 0, nz - 1, no persistent path, two steps or more); the instances' two-step arguments [parity], the
     // work list of (instance, tile, z segment) grouped by tile shape, and the
     // probe row tables
     int step_block = 2;
@@ -364,9 +364,10 @@ hipError_t kvs_launch_curl_state(kvs_ctx* c, const double* A);
 hipError_t kvs_launch_stable_dt(kvs_ctx* c, const double* dG, const double* drho, const double* deta,
                                 double* partial, int64_t npartial, double* out);
 
-// batched stepping (kvs_step.hip): refresh the device parameter table, then
-// replay (or capture) the graph of nsteps steps starting at b->step
-hipError_t kvs_batch_prepare(kvs_batch* b);
+// batched stepping (kvs_batch.hip): refresh the device parameter tables that a
+// run of nsteps steps takes, then replay (or capture) the graph of the steps
+// from b->step on
+hipError_t kvs_batch_prepare(kvs_batch* b, int64_t nsteps);
 hipError_t kvs_batch_trial_launch(kvs_batch* b);
 // Runs nsteps steps; *flips = launches that advanced the state (each swaps
 // the current and next buffers once).

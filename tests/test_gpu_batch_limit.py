@@ -56,3 +56,33 @@ def test_fullest_accepted_instance(kvs, dims, nprobes):
     assert np.abs(tr - tr0).max() <= 1e-12 * np.abs(tr0).max()
     for a, a0 in zip(st, st0):
         assert np.abs(a - a0).max() <= 1e-12 * np.abs(a0).max()
+
+
+@pytest.mark.parametrize("persistent,blocking,steps,tables", [
+    (True, 2, 40, 2),    # the run is one launch: parameters and the one-step work list
+    (False, 1, 40, 2),
+    (False, 2, 1, 2),
+    (False, 2, 2, 4),    # and those of the two-step launches
+])
+@pytest.mark.parametrize("eta", [0.5, 0.0], ids=["viscous", "lossless"])
+def test_two_step_tables_only_where_they_are_used(kvs, persistent, blocking, steps, tables, eta):
+    """Device buffers that the first run takes from the batch's allocator."""
+    import torch
+    h = 0.25e-3
+    print(f"case batch tables persistent {persistent} blocking {blocking} steps {steps}", flush=True)
+    stream = torch.cuda.Stream()
+    mem = kvs.TorchAllocator(0, stream.cuda_stream)
+    b = kvs.kvs_batch_create([(40, 3, 3, h, h, h), (9, 8, 7, h, h, h)], precision=kvs.KVS_FP32, sponge_cells=2,
+                             stream=stream.cuda_stream, allocator=mem)
+    try:
+        kvs.kvs_batch_set_persistent(b, persistent)
+        kvs.kvs_batch_set_step_blocking(b, blocking)
+        for i in range(2):
+            c = kvs.kvs_batch_instance(b, i)
+            kvs.kvs_set_material_uniform(c, 4e3, 1000.0, eta)
+            kvs.kvs_set_dt(c, 0.4 * kvs.kvs_stable_dt(c))
+        before = mem.allocs
+        kvs.kvs_batch_step(b, steps)
+        assert mem.allocs - before == tables
+    finally:
+        kvs.kvs_batch_destroy(b)
