@@ -607,6 +607,11 @@ kvs_status kvs_last_step_launch(const kvs_ctx* ctx, int32_t* kernel, int32_t* ti
  * (FP64: all but 2; with peak planes 0 and 3; grids of two rows more than the
  * tile) leave the choice to the model.  Every tile computes the same update. */
 kvs_status kvs_set_two_step_tile(kvs_ctx* ctx, int32_t tile);
+/* Tile of the one-step march of contexts with an absorbing layer (FP32,
+ * nx <= 257; elsewhere no effect): 1: 64 x 8 cells, 2: 128 x 8, 3: 192 x 5,
+ * 4: 256 x 4; 0: the tiled kernel instead; -1 (the default): kernel and tile by
+ * the context's size and medium; other values KVS_EINVAL. */
+kvs_status kvs_set_march_tile(kvs_ctx* ctx, int32_t tile);
 /* Time every variant on this context's grid, precision and medium, each with
  * the automatic z split and with 16-, 32- and 64-plane z segments
  * (trial_steps >= 1 launches each, after one untimed launch), and keep the

@@ -652,7 +652,7 @@ kvs_status kvs_step(kvs_ctx* c, int64_t nsteps) {
             c->launch_ev[0] = ea;
             c->launch_ev[1] = eb;
         }
-        const bool march = adv == 1 && kvs_step1_applies(c);
+        const bool march = adv == 1 && kvs_step1_applies(c, gn);
         const hipError_t le = adv == 2 ? kvs_launch_step2(c, gn, gn1)
                               : march  ? kvs_launch_step1(c, gn)
                                        : kvs_launch_step(c, gn);
@@ -1111,7 +1111,7 @@ kvs_status kvs_set_step_variant(kvs_ctx* c, int32_t v) {
     if (!c) return KVS_EINVAL;
     if (v < 0 || v >= kvs_step_variant_count()) return fail(c, KVS_EINVAL, "no such step variant");
     c->step_variant = v;
-    c->step1_off = v != 0 || c->step_zchunk != 0;
+    c->step1_use = v != 0 || c->step_zchunk != 0 ? 0 : -1;
     return KVS_OK;
 }
 
@@ -1122,7 +1122,7 @@ kvs_status kvs_set_step_tuning(kvs_ctx* c, int32_t v, int32_t zchunk, int32_t re
     c->step_variant = v;
     c->step_zchunk = c->step2_zchunk = zchunk;
     c->step_remap = remap != 0;
-    c->step1_off = v != 0 || zchunk != 0;
+    c->step1_use = v != 0 || zchunk != 0 ? 0 : -1;
     return KVS_OK;
 }
 
@@ -1137,6 +1137,13 @@ kvs_status kvs_set_two_step_tile(kvs_ctx* c, int32_t tile) {
     if (!c) return KVS_EINVAL;
     if (tile < -1 || tile > 3) return fail(c, KVS_EINVAL, "two-step tile must be -1..3");
     c->step2_tile = tile;
+    return KVS_OK;
+}
+
+kvs_status kvs_set_march_tile(kvs_ctx* c, int32_t tile) {
+    if (!c) return KVS_EINVAL;
+    if (tile < -1 || tile > 4) return fail(c, KVS_EINVAL, "march tile must be -1..4");
+    c->march_tile = tile;
     return KVS_OK;
 }
 
@@ -1217,18 +1224,18 @@ kvs_status kvs_autotune_step(kvs_ctx* c, int32_t trial_steps, int32_t* chosen, d
         if (ms_per_launch && v < cap) ms_per_launch[v] = v_best;
     }
     // the march takes the step of contexts with a layer unless a variant beat it
-    bool march_off = false;
+    int march = -1;
     if (kvs_step1_offered(c)) {
         double per = 0.0;
         const hipError_t e = trial(-1, &per);
         if (e != hipSuccess) return failed(e);
-        march_off = best_ms < per;
+        march = best_ms < per ? 0 : 1;
     }
     c->step_zchunk = best_z;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     c->step_variant = best;
-    c->step1_off = march_off;
+    c->step1_use = march;
     if (chosen) *chosen = best;
     return KVS_OK;
 }

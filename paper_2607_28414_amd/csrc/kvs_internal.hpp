@@ -168,9 +168,12 @@ struct kvs_ctx {
     int step_zchunk = 0;
     int step2_zchunk = 0;  // two-step launches: as set by kvs_set_step_tuning (the autotuner times one-step launches)
     int step_remap = 1;
-    // the tiled kernel also where the one-step march applies: the caller chose a
-    // variant or z split, or the autotuner timed both and the march was slower
-    bool step1_off = false;
+    // the one-step march of contexts with a layer: by rule (-1), not (0: the
+    // caller chose a variant or z split, or the autotuner timed both and the march
+    // was slower) or always (1: the autotuner, and it was faster); its tile (-1:
+    // by rule, 0: the tiled kernel)
+    int step1_use = -1;
+    int march_tile = -1;
     // steps per launch where the two-step kernel applies (1 or 2)
     int step_block = 2;
     int step2_tile = -1;  // tile shape of two-step launches where it is offered (-1: by the model of the march)
@@ -314,10 +317,10 @@ hipError_t kvs_launch_force_pattern(kvs_ctx* c, const kvs_force_pattern* p);
 // One FDTD step from (u[cur], w[cur]) into (u[1-cur], w[1-cur]) with source
 // amplitude gn (0: no force read).  Returns the launch error.
 hipError_t kvs_launch_step(kvs_ctx* c, double gn);
-// the same step on the two-step kernel's march: whether the context allows it
-// and it is the faster one by rule, and whether the tuning leaves it on
+// the same step on the two-step kernel's march: whether the context allows it,
+// and whether it takes a step with source amplitude gn
 bool kvs_step1_offered(const kvs_ctx* c);
-bool kvs_step1_applies(const kvs_ctx* c);
+bool kvs_step1_applies(const kvs_ctx* c, double gn);
 hipError_t kvs_launch_step1(kvs_ctx* c, double gn);
 // two steps in one launch (kvs_step2.hip) with source amplitudes gn, gn2:
 // whether the layer, probes and grid allow it, and whether the context is one

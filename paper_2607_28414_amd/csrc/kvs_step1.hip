@@ -215,16 +215,24 @@ hipError_t launch(kvs_ctx* c, StepArgs<float> a) {
     return hipGetLastError();
 }
 
-// The narrowest tile that spans the row (its last node needs no thread): such
-// a tile has no column halo.  190 x 161 x 175, us per step with the layer pass:
-// 192 x 5 171, 256 x 4 176, 64 x 8 179, 128 x 8 192; 128^3: 128 x 8 82, 64 x 8
-// 83, 256 x 4 86; 256^3: 256 x 4 427, 128 x 8 437, 64 x 8 461.
+// Large grids: the narrowest tile that spans the row (its last node needs no
+// thread): such a tile has no column halo.  190 x 161 x 175, us per step with the
+// layer pass: 192 x 5 171, 256 x 4 176, 64 x 8 179, 128 x 8 192; 128^3: 128 x 8 82,
+// 64 x 8 83, 256 x 4 86; 256^3: 256 x 4 427, 128 x 8 437, 64 x 8 461.  Below
+// kRowNodes nodes there are too few such blocks, and blocks of 1024 threads
+// march slower than those of 512: 64 x 8.  138 x 65 x 15: 192 x 5 35.0, 64 x 8
+// 27.7; 120 x 98 x 31: 128 x 8 31.0, 25.8; 203 x 97 x 29: 256 x 4 40.3, 34.4;
+// 171 x 114 x 71 (1.4 M nodes): 192 x 5 45.2, 47.2; 96 x 193 x 93: 52.7, 55.2.
+constexpr long long kRowNodes = 1200000;
 template <bool HET, bool VISC, bool FORCE>
 hipError_t launch_rows(kvs_ctx* c, const StepArgs<float>& a) {
-    if (a.nx <= 65) return launch<HET, VISC, FORCE, 1, 8>(c, a);
-    if (a.nx <= 129) return launch<HET, VISC, FORCE, 2, 8>(c, a);
-    if (a.nx <= 193) return launch<HET, VISC, FORCE, 3, 5>(c, a);
-    return launch<HET, VISC, FORCE, 4, 4>(c, a);
+    const int by_rule = a.N < kRowNodes || a.nx <= 65 ? 1 : a.nx <= 129 ? 2 : a.nx <= 193 ? 3 : 4;
+    switch (c->march_tile > 0 ? c->march_tile : by_rule) {
+        case 1: return launch<HET, VISC, FORCE, 1, 8>(c, a);
+        case 2: return launch<HET, VISC, FORCE, 2, 8>(c, a);
+        case 3: return launch<HET, VISC, FORCE, 3, 5>(c, a);
+        default: return launch<HET, VISC, FORCE, 4, 4>(c, a);
+    }
 }
 
 template <bool HET, bool VISC>
@@ -241,7 +249,22 @@ bool kvs_step1_offered(const kvs_ctx* c) {
            c->grid.nx * c->grid.ny < ((int64_t)1 << 30) - 1024;
 }
 
-bool kvs_step1_applies(const kvs_ctx* c) { return kvs_step1_offered(c) && !c->step1_off; }
+// On small grids a step is a short chain of launches, loads and barriers, and
+// where a thread has little to do besides, the tiled kernel's smaller blocks
+// end first.  us per step with the layer pass, march and tiled kernel: lossless
+// 118 x 14 x 61 23.1 / 21.9, 33 x 29 x 104 21.7 / 20.6, 105 x 31 x 51 20.6 / 19.7;
+// heterogeneous with force on the step 138 x 65 x 15 27.7 / 26.1, 256 x 24 x 20
+// 25.7 / 24.3; viscous without, 186 x 25 x 12 22.8 / 23.8, 100 x 44 x 14 21.7 / 22.6;
+// lossless 60 x 90 x 59 21.8 / 24.9.  Of 220 grids of 10^3 to 6 10^6 nodes two are
+// more than 2 % slower with the march than with the tiled kernel by this rule
+// (4 and 3 %); with tiles that span the row on all of them 54 were, by up to 25 %.
+constexpr int64_t kMarchNodes = 250000;
+bool kvs_step1_applies(const kvs_ctx* c, double gn) {
+    if (!kvs_step1_offered(c) || c->march_tile == 0) return false;
+    if (c->march_tile > 0) return true;
+    if (c->step1_use >= 0) return c->step1_use == 1;
+    return c->N >= kMarchNodes || (c->viscous && !(c->hetero && gn != 0.0));
+}
 
 hipError_t kvs_launch_step1(kvs_ctx* c, double gn) {
     const kvs_grid& g = c->grid;

@@ -195,6 +195,7 @@ SIGNATURES = {
     "kvs_autotune_step": ([_P, C.c_int32, C.POINTER(C.c_int32), _D, C.c_int32], C.c_int),
     "kvs_set_step_blocking": ([_P, C.c_int32], C.c_int),
     "kvs_set_two_step_tile": ([_P, C.c_int32], C.c_int),
+    "kvs_set_march_tile": ([_P, C.c_int32], C.c_int),
     "kvs_last_step_launch": ([_P, C.POINTER(C.c_int32), C.POINTER(C.c_int32)], C.c_int),
     "kvs_set_direction_precision": ([_P, C.c_int32], C.c_int),
     "kvs_set_residual_precision": ([_P, C.c_int32], C.c_int),
@@ -562,6 +563,11 @@ def kvs_set_step_blocking(ctx, steps):
 def kvs_set_two_step_tile(ctx, tile):
     """Tile of two-step launches: 0 128x8, 1 64x16, 2 64x8, 3 192x5, -1 automatic."""
     _check(lib().kvs_set_two_step_tile(ctx, int(tile)), ctx)
+
+
+def kvs_set_march_tile(ctx, tile):
+    """Tile of layer contexts' one-step march: 1 64x8, 2 128x8, 3 192x5, 4 256x4, 0 the tiled kernel, -1 automatic."""
+    _check(lib().kvs_set_march_tile(ctx, int(tile)), ctx)
 
 
 def kvs_last_step_launch(ctx):

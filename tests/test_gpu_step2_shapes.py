@@ -92,12 +92,68 @@ def test_every_tile_matches_one_step_bitwise(kvs, tile, edge, fp64, peaks, het, 
         assert np.array_equal(a, b), n
 
 
-def last_launch(kvs, dims, prec=None, pml=0, steps=2, tile=-1, zchunk=None, probe=None):
+MARCH = [(64, 8), (128, 8), (192, 5), (256, 4)]
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3, 4])
+@pytest.mark.parametrize("edge", range(4))
+@pytest.mark.parametrize("het", [True, False], ids=["maps", "uniform"])
+@pytest.mark.parametrize("visc", [True, False], ids=["viscous", "lossless"])
+def test_every_march_tile_matches_the_tiled_kernel_bitwise(kvs, tile, edge, het, visc):
+    """The one-step march of contexts with a layer: each tile on rows it spans, on
+    rows one node longer (a second tile of few cells) and on the longest, with
+    whole and broken tiles of rows, force and probes."""
+    X, R = MARCH[tile - 1]
+    nx, ny, nz = [(X, R + 2, 9), (min(X + 1, 257), 2 * R + 2, 13), (min(X + 2, 257), 2 * R + 3, 9), (257, 3 * R + 1, 10)][edge]
+    ny = max(ny, 9)
+    shape = (nz, ny, nx)
+    print(f"case march tile {MARCH[tile - 1]} grid {nx}x{ny}x{nz} het {het} visc {visc}", flush=True)
+    out = []
+    for t in (0, tile):
+        rng = np.random.default_rng([nx, ny, nz])
+        ctx = kvs.kvs_create((nx, ny, nz) + (0.25e-3,) * 3, precision=kvs.KVS_FP32, sponge_cells=0)
+        try:
+            eta = 0.8 if visc else 0.0
+            if het:
+                kvs.kvs_set_material(ctx, 1e3 * (1 + 5 * rng.random(shape)), 950 + 100 * rng.random(shape),
+                                     eta * rng.random(shape))
+            else:
+                kvs.kvs_set_material_uniform(ctx, 3e3, 1000.0, eta)
+            kvs.kvs_set_dt(ctx, 0.4 * kvs.kvs_stable_dt(ctx))
+            kvs.kvs_set_projected_force(ctx, 1e3 * rng.standard_normal((3,) + shape))
+            kvs.kvs_set_envelope(ctx, [1.0, 0.5, 0.0, 0.25])
+            kvs.kvs_set_pml(ctx, 3)
+            kvs.kvs_set_probes(ctx, [[i, ny // 2, nz // 2] for i in range(nx)] + [[0, 0, 0]], 3)
+            kvs.kvs_set_march_tile(ctx, t)
+            kvs.kvs_step(ctx, 5)
+            kvs.kvs_step(ctx, 4)
+            kernel, launched = kvs.kvs_last_step_launch(ctx)
+            assert kernel == (kvs.KVS_STEP_MARCH if t else kvs.KVS_STEP_TILED)
+            assert not t or launched[:2] == (X, R)
+            out.append(list(kvs.kvs_get_state(ctx, shape)[:2]) + [kvs.kvs_read_traces(ctx, nx + 1, 3)])
+        finally:
+            kvs.kvs_destroy(ctx)
+    assert np.abs(out[0][0]).max() > 0
+    for n, (a, b) in enumerate(zip(*out)):
+        assert np.array_equal(a, b), n
+
+
+def last_launch(kvs, dims, prec=None, pml=0, steps=2, tile=-1, zchunk=None, probe=None, eta=0.5, het=False, force=False,
+                march=-1):
     ctx = kvs.kvs_create(dims + (0.3e-3,) * 3, precision=kvs.KVS_FP32 if prec is None else prec, sponge_cells=0)
     try:
         assert kvs.kvs_last_step_launch(ctx)[0] == kvs.KVS_STEP_NONE
-        kvs.kvs_set_material_uniform(ctx, 3e3, 1000.0, 0.5)
+        one = np.ones(dims[::-1])
+        if het:
+            one[0] *= 2
+            kvs.kvs_set_material(ctx, 3e3 * one, 1000.0 * one, eta * one)
+        else:
+            kvs.kvs_set_material_uniform(ctx, 3e3, 1000.0, eta)
         kvs.kvs_set_dt(ctx, 0.4 * kvs.kvs_stable_dt(ctx))
+        if force:
+            kvs.kvs_set_projected_force(ctx, np.ones((3,) + dims[::-1]))
+            kvs.kvs_set_envelope(ctx, np.ones(steps))
+        kvs.kvs_set_march_tile(ctx, march)
         if pml:
             kvs.kvs_set_pml(ctx, pml)
         if probe:
@@ -122,12 +178,25 @@ def test_which_kernel_steps(kvs):
     assert last_launch(kvs, (40, 10, 20), prec=kvs.KVS_FP64)[0] == tiled  # 64 x 8 is the only FP64 tile
     assert last_launch(kvs, (40, 10, 20))[0] == two
     assert last_launch(kvs, (40, 10, 20), tile=2)[1][:2] in [(64, 16), (192, 5)]  # eight rows are not offered
-    # contexts with an absorbing layer
-    for nx, tile in ((9, (64, 8)), (65, (64, 8)), (66, (128, 8)), (130, (192, 5)), (194, (256, 4)), (257, (256, 4))):
-        k, t = last_launch(kvs, (nx, 12, 11), pml=2)
+    # contexts with an absorbing layer: 64 x 8 on small grids, else a tile that spans the row
+    assert last_launch(kvs, (130, 12, 11), pml=2)[1][:2] == (64, 8)
+    for nx, tile in ((100, (128, 8)), (130, (192, 5)), (194, (256, 4)), (257, (256, 4))):
+        dims = (nx, 110, 1 + 1200000 // (110 * nx))
+        k, t = last_launch(kvs, dims, pml=2)
         assert k == march and t[:2] == tile, nx
-    assert last_launch(kvs, (258, 12, 11), pml=2)[0] == tiled            # longer than any tile
+        assert last_launch(kvs, dims, pml=2, eta=0.0, het=True, force=True)[0] == march
+    small = (60, 40, 104)  # 249600 nodes
+    for dims, kernel in ((small, tiled), ((60, 40, 105), march)):
+        assert last_launch(kvs, dims, pml=2, eta=0.0)[0] == kernel
+        assert last_launch(kvs, dims, pml=2, het=True, force=True)[0] == kernel
+    assert last_launch(kvs, small, pml=2, het=True)[0] == march
+    assert last_launch(kvs, small, pml=2, force=True)[0] == march
+    assert last_launch(kvs, small, pml=2, eta=0.0, march=3) == (march, last_launch(kvs, small, pml=2, march=3)[1])
+    assert last_launch(kvs, (130, 12, 11), pml=2, march=0)[0] == tiled
+    assert last_launch(kvs, (258, 12, 11), pml=2, march=1)[0] == tiled   # longer than any tile
     assert last_launch(kvs, (66, 12, 11), prec=kvs.KVS_FP64, pml=2)[0] == tiled
     assert last_launch(kvs, (66, 12, 11), pml=2, zchunk=5) == (tiled, (64, 4, 5))  # the caller's own tuning
     with pytest.raises(kvs.KvsError):
         last_launch(kvs, (9, 9, 9), tile=4)
+    with pytest.raises(kvs.KvsError):
+        last_launch(kvs, (9, 9, 9), march=5)
