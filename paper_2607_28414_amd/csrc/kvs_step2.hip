@@ -24,12 +24,21 @@ __global__ __launch_bounds__(64 * WX * R) void step2_kernel(const Step2Args<T> A
     step2_tile<T, HET, VISC, FORCE, PEAK, WX, R>(A2, &pk, lds, t % a.gx, (t / a.gx) % a.gy, t / (a.gx * a.gy));
 }
 
-// Tile and z segment of a launch: the shape whose blocks finish first by a
-// model of its march, rounds of resident blocks x (planes + 3 to fill the
-// queues) x the time of a plane, which is the larger of a floor (the latency
-// of loads, barrier and LDS) and the wavefronts' work on a CU, one unit per
-// wavefront and update.  Unit 80 ns (256^3 heterogeneous: 28 units, 2.2 us a
-// plane), floor 9 units (0.7 us: small grids).
+// Tile and z segment of a launch: the ones whose blocks finish first by a model
+// of the march, rounds of resident blocks x (planes + 3 to fill the queues) x the
+// time of a plane.  That time is a latency (loads, barrier and LDS) and the
+// wavefronts' work on a CU, 80 ns per wavefront and update (256^3 heterogeneous:
+// 28 units, 2.2 us a plane).  A shape's segments are compared with the larger of
+// the work and kPlaneFloor units (0.7 us, small grids), which favours few long
+// ones; shapes with the sum of the work and kPlaneStart units: compared as
+// segments are, 64 x 8 was taken at 128^3 heterogeneous (21 + 3 planes of 14 units,
+// 22.0 us a step) where 128 x 8 (11 + 3 planes of 28) takes 19.7 and 64 x 16
+// (9 + 3 of 30) 20.1; 90 x 65 x 269 21.9 / 18.0 (128 x 8); 100 x 165 x 71 uniform
+// 13.1 / 10.0 (64 x 16).  Over 252 viscous grids up to 256^3 a start of 6 to 9
+// units gave 1.036 to 1.039x in the geometric mean and none slower, 12 and more
+// made some slower.
+constexpr double kPlaneFloor = 9.0, kPlaneStart = 6.0;
+
 struct Step2Plan {
     double cost = 1e300;
     int shape = -1, gx = 1, gy = 1, kchunk = 1;
@@ -43,16 +52,22 @@ void consider(Step2Plan& best, int shape, int only, const kvs_grid& g, int cap, 
     const double units = step2_units(shape);
     const int per_cu = std::max(1, cap / 256);
     const int max_seg = std::max(1, planes / 2);
+    double least = 1e300;
+    Step2Plan p;
     for (int seg = 1; seg <= max_seg; ++seg) {
         int chunk = (planes + seg - 1) / seg;
         if (zchunk > 0) chunk = std::min(zchunk, planes);
         const long long blocks = (long long)gx * gy * ((planes + chunk - 1) / chunk);
         const long long rounds = (blocks + cap - 1) / cap;
         const double on_cu = (double)std::min<long long>(per_cu, (blocks + 255) / 256);
-        const double cost = (double)rounds * (chunk + 3) * std::max(9.0, units * on_cu);
-        if (cost < best.cost * 0.999) best = {cost, shape, gx, gy, chunk};
+        const double march = (double)rounds * (chunk + 3), cost = march * std::max(kPlaneFloor, units * on_cu);
+        if (cost < least * 0.999) {
+            least = cost;
+            p = {march * (kPlaneStart + units * on_cu), shape, gx, gy, chunk};
+        }
         if (zchunk > 0) break;
     }
+    if (p.cost < best.cost * 0.999) best = p;
 }
 
 template <typename T, bool HET, bool VISC, bool FORCE, int S, bool PEAK = false>

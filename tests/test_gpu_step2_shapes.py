@@ -178,6 +178,8 @@ def test_which_kernel_steps(kvs):
     assert last_launch(kvs, (40, 10, 20), prec=kvs.KVS_FP64)[0] == tiled  # 64 x 8 is the only FP64 tile
     assert last_launch(kvs, (40, 10, 20))[0] == two
     assert last_launch(kvs, (40, 10, 20), tile=2)[1][:2] in [(64, 16), (192, 5)]  # eight rows are not offered
+    # 22.0 us a step with 64 x 8, 19.7 and 20.1 with these
+    assert last_launch(kvs, (128, 128, 128), het=True)[1][:2] in [(128, 8), (64, 16)]
     # contexts with an absorbing layer: 64 x 8 on small grids, else a tile that spans the row
     assert last_launch(kvs, (130, 12, 11), pml=2)[1][:2] == (64, 8)
     for nx, tile in ((100, (128, 8)), (130, (192, 5)), (194, (256, 4)), (257, (256, 4))):
