@@ -715,14 +715,7 @@ __global__ __launch_bounds__(kSmallMaxThreads) void batch_small_kernel(const Bat
     T* du = (nsteps & 1) ? a.un : const_cast<T*>(a.u);
     T* dw = (nsteps & 1) ? a.wn : const_cast<T*>(a.w);
     if constexpr (LINE) {
-        // the cells from the registers, the Dirichlet layer as it was
-        if (nsteps & 1)
-            for (int c = 0; c < 3; ++c)
-                for (int g = threadIdx.x; g < N; g += nthr) {
-                    if (g >= row + 1 && g <= row + nx - 2) continue;
-                    du[c * N + g] = a.u[c * N + g];
-                    dw[c * N + g] = a.w[c * N + g];
-                }
+        // the cells from the registers; the Dirichlet layer of both buffers is 0
 #pragma unroll
         for (int m = 0; m < CPT; ++m)
             if (cell[m] >= 0)
