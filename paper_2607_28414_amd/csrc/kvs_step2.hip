@@ -26,48 +26,56 @@ __global__ __launch_bounds__(64 * WX * R) void step2_kernel(const Step2Args<T> A
 
 // Tile and z segment of a launch: the ones whose blocks finish first by a model
 // of the march, rounds of resident blocks x (planes + 3 to fill the queues) x the
-// time of a plane.  That time is a latency (loads, barrier and LDS) and the
-// wavefronts' work on a CU, 80 ns per wavefront and update (256^3 heterogeneous:
-// 28 units, 2.2 us a plane).  A shape's segments are compared with the larger of
-// the work and kPlaneFloor units (0.7 us, small grids), which favours few long
-// ones; shapes with the sum of the work and kPlaneStart units: compared as
-// segments are, 64 x 8 was taken at 128^3 heterogeneous (21 + 3 planes of 14 units,
-// 22.0 us a step) where 128 x 8 (11 + 3 planes of 28) takes 19.7 and 64 x 16
-// (9 + 3 of 30) 20.1; 90 x 65 x 269 21.9 / 18.0 (128 x 8); 100 x 165 x 71 uniform
-// 13.1 / 10.0 (64 x 16).  Over 252 viscous grids up to 256^3 a start of 6 to 9
-// units gave 1.036 to 1.039x in the geometric mean and none slower, 12 and more
-// made some slower.
+// time of a plane, the larger of a floor (the latency of loads, barrier and LDS)
+// and the wavefronts' work on a CU, one unit per wavefront and update.  Unit 80 ns
+// (256^3 heterogeneous: 28 units, 2.2 us a plane), floor 9 units (0.7 us: small
+// grids).  Shapes whose march is short (kShortMarch planes) are compared with
+// kPlaneStart units added to the work of a plane instead: without, 64 x 8 was taken
+// at 128^3 heterogeneous (21 + 3 planes of 14 units, 22.0 us a step) where 128 x 8
+// (11 + 3 planes of 28) takes 19.7 and 64 x 16 (9 + 3 of 30) 20.1; 90 x 65 x 269
+// 21.9 / 18.0 (128 x 8); 100 x 165 x 71 uniform 13.1 / 10.0 (64 x 16).  Over 252
+// viscous grids up to 256^3 6 to 9 units gave 1.036 to 1.039x in the geometric
+// mean and none slower, 12 and more made some slower.  In a long march the start
+// is hidden: 384 x 384 x 512 with force, 513 planes of 192 x 5 or 420 of 64 x 16,
+// takes 0.75 ms a step with the former and 0.85 with the latter, which the added
+// units would choose.
 constexpr double kPlaneFloor = 9.0, kPlaneStart = 6.0;
+constexpr long long kShortMarch = 100;
 
 struct Step2Plan {
-    double cost = 1e300;
+    double cost = 1e300, short_cost = 1e300;
+    long long march = 0;
     int shape = -1, gx = 1, gy = 1, kchunk = 1;
 };
 
+// The plans of the shapes offered so far: the best by either cost.
+struct Step2Plans {
+    Step2Plan by_work, by_start;
+    const Step2Plan& best() const { return by_work.march <= kShortMarch ? by_start : by_work; }
+};
+
 // only: the shape asked for, where the context offers it, else -1
-void consider(Step2Plan& best, int shape, int only, const kvs_grid& g, int cap, int zchunk) {
+void consider(Step2Plans& plans, int shape, int only, const kvs_grid& g, int cap, int zchunk) {
     if (!step2_offers(shape, g.ny) || (only >= 0 && shape != only)) return;
     const int planes = (int)g.nz - 2;
     const int gx = overlap_tiles((int)g.nx, 64 * kStep2Wx[shape]), gy = overlap_tiles((int)g.ny, kStep2Rows[shape]);
     const double units = step2_units(shape);
     const int per_cu = std::max(1, cap / 256);
     const int max_seg = std::max(1, planes / 2);
-    double least = 1e300;
     Step2Plan p;
     for (int seg = 1; seg <= max_seg; ++seg) {
         int chunk = (planes + seg - 1) / seg;
         if (zchunk > 0) chunk = std::min(zchunk, planes);
         const long long blocks = (long long)gx * gy * ((planes + chunk - 1) / chunk);
         const long long rounds = (blocks + cap - 1) / cap;
-        const double on_cu = (double)std::min<long long>(per_cu, (blocks + 255) / 256);
-        const double march = (double)rounds * (chunk + 3), cost = march * std::max(kPlaneFloor, units * on_cu);
-        if (cost < least * 0.999) {
-            least = cost;
-            p = {march * (kPlaneStart + units * on_cu), shape, gx, gy, chunk};
-        }
+        const double work = units * (double)std::min<long long>(per_cu, (blocks + 255) / 256);
+        const long long march = rounds * (chunk + 3);
+        const double cost = (double)march * std::max(kPlaneFloor, work);
+        if (cost < p.cost * 0.999) p = {cost, (double)march * (kPlaneStart + work), march, shape, gx, gy, chunk};
         if (zchunk > 0) break;
     }
-    if (p.cost < best.cost * 0.999) best = p;
+    if (p.cost < plans.by_work.cost * 0.999) plans.by_work = p;
+    if (p.short_cost < plans.by_start.short_cost * 0.999) plans.by_start = p;
 }
 
 template <typename T, bool HET, bool VISC, bool FORCE, int S, bool PEAK = false>
@@ -99,17 +107,20 @@ int shape_cap() {
 template <typename T, bool HET, bool VISC, bool FORCE>
 hipError_t launch_medium(kvs_ctx* c, Step2Args<T>& A2, const Step2Peaks<T>& pk) {
     const kvs_grid& g = c->grid;
-    Step2Plan p;
+    Step2Plans plans;
     const int want = c->step2_tile;
     const bool has = sizeof(T) == 8 ? want == 2 : want >= 0 && (pk.n == 0 || want == 1 || want == 2);
     const int only = has && step2_offers(want, g.ny) ? want : -1;
     // peak maps: the shape that fits most row lengths (FP32: 64 x 16), compiled
-    // for them alone; 64 x 8 where the grid's rows rule that out
+    // for them alone; 64 x 8 where the grid's rows rule that out.  Resident blocks
+    // as without maps, which holds but for 64 x 8 heterogeneous viscous (one block
+    // on a CU for two); rounds x blocks on a CU come out the same there
     if constexpr (sizeof(T) == 4) {
-        if (pk.n > 0) consider(p, 1, only, g, shape_cap<T, HET, VISC, FORCE, 1>(), c->step2_zchunk);
+        if (pk.n > 0) consider(plans, 1, only, g, shape_cap<T, HET, VISC, FORCE, 1>(), c->step2_zchunk);
     }
-    if (pk.n > 0 && p.shape < 0) consider(p, 2, only, g, shape_cap<T, HET, VISC, FORCE, 2>(), c->step2_zchunk);
-    if (p.shape >= 0) {
+    if (pk.n > 0 && plans.by_work.shape < 0) consider(plans, 2, only, g, shape_cap<T, HET, VISC, FORCE, 2>(), c->step2_zchunk);
+    if (pk.n > 0) {
+        const Step2Plan& p = plans.best();
         A2.a.gx = p.gx;
         A2.a.gy = p.gy;
         A2.a.kchunk = p.kchunk;
@@ -119,11 +130,12 @@ hipError_t launch_medium(kvs_ctx* c, Step2Args<T>& A2, const Step2Peaks<T>& pk) 
         return launch_shape<T, HET, VISC, FORCE, 2, true>(c, A2, pk);
     }
     if constexpr (sizeof(T) == 4) {
-        consider(p, 0, only, g, shape_cap<T, HET, VISC, FORCE, 0>(), c->step2_zchunk);
-        consider(p, 1, only, g, shape_cap<T, HET, VISC, FORCE, 1>(), c->step2_zchunk);
-        consider(p, 3, only, g, shape_cap<T, HET, VISC, FORCE, 3>(), c->step2_zchunk);
+        consider(plans, 0, only, g, shape_cap<T, HET, VISC, FORCE, 0>(), c->step2_zchunk);
+        consider(plans, 1, only, g, shape_cap<T, HET, VISC, FORCE, 1>(), c->step2_zchunk);
+        consider(plans, 3, only, g, shape_cap<T, HET, VISC, FORCE, 3>(), c->step2_zchunk);
     }
-    consider(p, 2, only, g, shape_cap<T, HET, VISC, FORCE, 2>(), c->step2_zchunk);
+    consider(plans, 2, only, g, shape_cap<T, HET, VISC, FORCE, 2>(), c->step2_zchunk);
+    const Step2Plan& p = plans.best();
     A2.a.gx = p.gx;
     A2.a.gy = p.gy;
     A2.a.kchunk = p.kchunk;
@@ -197,8 +209,13 @@ hipError_t launch_t(kvs_ctx* c, double gn, double gn2) {
 }  // namespace
 
 bool kvs_step2_supported(const kvs_ctx* c) {
-    // cell offsets within a field are 32-bit, byte offsets within a plane too;
-    // FP64 has one tile shape
+    // wherever the launch can be made: cell offsets within a field are 32-bit, byte
+    // offsets within a plane too; FP64 has one tile shape.  us per step against
+    // the tuned one-step kernel, heterogeneous viscous FP32, without and with three
+    // peak planes: 500 x 500 x 640 1322 / 2266, 1366 / 2276; 512 x 512 x 640, whose
+    // planes are 1 MiB apart, 1813 / 1830, 1845 / 1863; 512 x 256 x 512 684 / 744,
+    // 692 / 753; of 340 contexts of every medium, precision, with and without
+    // force, none slower than before two steps shared a launch
     const int64_t plane = c->grid.nx * c->grid.ny * (c->prec == KVS_FP32 ? 4 : 8);
     return c->pml_cells == 0 && c->N < ((int64_t)1 << 31) && plane < ((int64_t)1 << 32) - 4096 &&
            (c->nprobes == 0 || c->probe_rows_ok) && (c->prec == KVS_FP32 || step2_offers(2, c->grid.ny));

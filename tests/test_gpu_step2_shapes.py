@@ -143,8 +143,8 @@ def last_launch(kvs, dims, prec=None, pml=0, steps=2, tile=-1, zchunk=None, prob
     ctx = kvs.kvs_create(dims + (0.3e-3,) * 3, precision=kvs.KVS_FP32 if prec is None else prec, sponge_cells=0)
     try:
         assert kvs.kvs_last_step_launch(ctx)[0] == kvs.KVS_STEP_NONE
-        one = np.ones(dims[::-1])
         if het:
+            one = np.ones(dims[::-1])
             one[0] *= 2
             kvs.kvs_set_material(ctx, 3e3 * one, 1000.0 * one, eta * one)
         else:
@@ -180,6 +180,8 @@ def test_which_kernel_steps(kvs):
     assert last_launch(kvs, (40, 10, 20), tile=2)[1][:2] in [(64, 16), (192, 5)]  # eight rows are not offered
     # 22.0 us a step with 64 x 8, 19.7 and 20.1 with these
     assert last_launch(kvs, (128, 128, 128), het=True)[1][:2] in [(128, 8), (64, 16)]
+    # a long march: 0.75 ms a step with force against 0.85 with 64 x 16
+    assert last_launch(kvs, (384, 384, 512))[1][:2] == (192, 5)
     # contexts with an absorbing layer: 64 x 8 on small grids, else a tile that spans the row
     assert last_launch(kvs, (130, 12, 11), pml=2)[1][:2] == (64, 8)
     for nx, tile in ((100, (128, 8)), (130, (192, 5)), (194, (256, 4)), (257, (256, 4))):
