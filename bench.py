@@ -71,22 +71,22 @@ HBM_PEAK_GBS = 8000.0
 # scaled by what it reads for a plain copy of known size (--copy-calibration):
 # FETCH_SIZE reports half of the bytes a copy reads, WRITE_SIZE all of the
 # bytes it writes.  A changed source voids the figures (traffic -> null).
-STEP_SOURCE_SHA = "87f33e7e0ce90b1bd691da323d70afcd16b4918196681a00198047e267eda671"
+STEP_SOURCE_SHA = "c0e17394b712b604b4f3f153b3aa93962b9c5fb307ec29051eecf9d9c4b8a94d"
 STEP_COUNTERS_KIB = {  # variant -> (FETCH_SIZE, WRITE_SIZE), mean of 6 dispatches
-    0: (423999.4, 390146.0),
-    1: (399713.7, 390146.0),
-    2: (323288.3, 390146.0),
-    3: (302645.5, 390146.0),
-    4: (356112.1, 390146.0),
-    5: (331558.2, 390146.0),
-    6: (304019.3, 390146.8),
-    7: (304534.2, 390148.7),
+    0: (423732.6, 390146.0),
+    1: (399941.3, 390146.0),
+    2: (321992.5, 390146.0),
+    3: (302670.1, 390146.1),
+    4: (361286.7, 390146.0),
+    5: (331853.5, 390146.0),
+    6: (303921.6, 390146.6),
+    7: (304662.1, 390146.2),
 }
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 # The same counters for the two-step kernel (step2_kernel, one launch = two
 # steps without force), taken on STEP2_SOURCES with SHA-256 STEP2_SOURCE_SHA.
-STEP2_SOURCE_SHA = "45e5eee20eccad1eeb402c42afa6ea6763343aab7f66ebb361d323f3f5b1b97e"
-STEP2_COUNTERS_KIB = (329553.0, 387138.1)  # (FETCH_SIZE, WRITE_SIZE), mean of 6 dispatches
+STEP2_SOURCE_SHA = "b185b512f29c2fc3d289c3ebad3267350e78546676d2883e6dc3e4d5d1e7105d"
+STEP2_COUNTERS_KIB = (329645.0, 387139.0)  # (FETCH_SIZE, WRITE_SIZE), mean of 6 dispatches
 # Algorithmic FP32 arithmetic of one heterogeneous viscous cell-update of the
 # summed-form leapfrog (Sec. 3.1), an FMA counted as two: six harmonic face
 # moduli 2 G G' / (G + G') / h^2 (5 each, 30); the sponge factors s,

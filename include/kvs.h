@@ -506,7 +506,11 @@ void kvs_unet_destroy(kvs_unet* net);
 const char* kvs_unet_last_error(const kvs_unet* net);
 /* FP32 master weights, layer by layer in network order, each [co][27 * ci]
  * with k = tap * ci + c, tap = 9 (dz + 1) + 3 (dy + 1) + (dx + 1); the
- * pointwise projection is [1][ci]. */
+ * pointwise projection is [1][ci].  kvs_unet_set_weights and
+ * kvs_unet_adam_step rewrite what the network reads and return when that is
+ * done; they wait for the blocking streams (and adam_step for its own), not for
+ * work on the network queued on other non-blocking streams, which the caller
+ * finishes first. */
 int64_t kvs_unet_num_weights(const kvs_unet* net);
 /* Layers in network order: input / output channels, dilation (0 for the
  * pointwise projection) and taps (27 or 1) of layer l. */

@@ -23,23 +23,25 @@
 // the next pair is rounded.
 //
 // When the first of the two iterations already ends the solve (tolerance, a
-// fixed or the largest count) or p1.A p1 is not positive, the update applies
-// that iteration alone (phi += a0 p, r = r1, p stays p); the next pair then
+// fixed or the largest count), takes the residual so far down that r1.r1 has no
+// digits left (kPairFall), or p1.A p1 is not positive, the update applies that
+// iteration alone (phi += a0 p, r = r1, p stays p); the next pair then
 // meets the breakdown itself.
 //
 // Tiles: 64 WX x R threads, all forming q, the inner ones (and those next to
 // a wall) owning their cells (overlap_tiles); z is marched with A q one plane
 // behind q, so one barrier per plane orders both stages.  Loads are issued two
-// planes ahead into two named register sets (the march is unrolled by two):
-// one plane ahead the sums sweep took 260 instead of 213 us at 384 x 384 x 512.
-// The tiles are held to 64 registers, so that two blocks of 1024 threads share
-// a CU: with 68 the update took 109 instead of 98 us at 256^3.
+// planes ahead into two named register sets (the march is unrolled by two), so
+// that no wait is for a load of the plane before.  The tiles are held to 64
+// registers, so that two blocks of 1024 threads share a CU: without the limit
+// (68) the sweeps take 65 + 129 us at 256^3 instead of 60 + 120 (at 384 x 384 x 512
+// 238 + 680 instead of 260 + 722).
 //
-// Measured at 256^3: 58 us (sums; the 134 MB that it reads are mostly in the
-// 256 MB cache, LDS and FP64 issue bound it) + 119 us (update; 537 MB, 4.5
-// TB/s: what HBM delivers to as many writes as reads) for two iterations,
-// where two pairs of one-iteration sweeps with their scalar kernels took
-// 262 us; 1e-8 in 904 iterations: 82 instead of 118 ms.
+// Measured at 256^3: 60 us (sums; 134 MB algorithmic, 156 MB fetched, mostly from
+// the 256 MB cache: LDS and FP64 issue bound it) + 120 us (update; 537 MB
+// algorithmic, 342 MB fetched and 266 MB written, 5.1 TB/s: HBM bounds it) for two
+// iterations, where two pairs of one-iteration sweeps with their scalar kernels
+// took 262 us; 1e-8 in 904 iterations: 82 instead of 118 ms.
 #include <type_traits>
 
 #include "kvs_cg_pair.hpp"
@@ -234,9 +236,8 @@ struct PairShape {
 
 // The tile with the fewest threads over the grid's rows, whole tiles counted
 // (the first stage is formed by all of them).  Measured, us per update sweep:
-// 256 x 256 x 256 101 (2 x 8), 123 (1 x 16), 145 (1 x 8); 160 x 144 x 208 43,
-// 37, 37; 240 x 200 x 200 66, 63, 77; four wavefronts a row and four rows were
-// never the best (126, 47, 74).
+// 256 x 256 x 256 120 (2 x 8), 149 (1 x 16), 170 (1 x 8); 160 x 144 x 208 54,
+// 48, 51; 240 x 200 x 200 84, 77, 89.
 PairShape pair_shape(int nx, int ny) {
     constexpr PairShape shapes[] = {{2, 8}, {1, 16}, {1, 8}};
     PairShape best = shapes[0];

@@ -77,7 +77,14 @@ inline int choose_kchunk(int xytiles, int planes, int cap) {
 
 // Shortest z segments of the CG sweeps.  Where segments of 8 planes leave the
 // chip short of blocks, a sweep's time is its blocks' serial march, not their
-// halo planes, so segments of 2 planes are allowed.
+// halo planes, so segments of 2 planes are allowed: while 8-plane segments are
+// 1024 blocks or fewer.  us per iteration with segments of 8 planes and more, and
+// with short ones (blocks at 8 planes): FP32 48^3 (24) 17.4, 11.9; 96^3 (168) 18.1,
+// 16.0; 128^3 (288) 20.3, 20.4; FP64 64^3 (64) 20.9, 14.0; 96^3 (288) 28.2, 22.9;
+// 144^3 (972) 55.5, 50.9.  Beyond the line halo planes begin to count, but by the
+// model below short segments still are no slower up to 3500 blocks: FP64 160 x 144 x
+// 208 (1404) 75.6, 70.3; 192^3 (1728) 96.3, 90.6; FP32 320 x 256 x 256 (3456) 157,
+// 147; 240 x 200 x 200, 224^3, 256^3 the same.
 inline int cg_min_planes(int xytiles, int planes) { return (long long)xytiles * ((planes + 7) / 8) <= 1024 ? 2 : 8; }
 
 // z segment of a CG sweep.  Where short segments are allowed: the one with the

@@ -2176,9 +2176,10 @@ kvs_status ufail(kvs_unet* u, kvs_status s, const std::string& m) {
 }
 
 // BF16 forward and transposed layouts, FP32 projection, output and composed
-// weights of the device's master weights, on the legacy default stream (after
-// what other streams still read) and complete on return.  A host loop over the
-// 0.3 M weights and seven copies took 4.1 ms of every training step.
+// weights of the device's master weights, on the legacy default stream and
+// complete on return.  Work on the network that non-blocking streams still have
+// queued is not waited for: the caller has to have finished it.  A host loop over
+// the 0.3 M weights and seven copies took 4.1 ms of every training step.
 kvs_status upload_weights(kvs_unet* u) {
     const int nl = (int)u->layers.size();
     PrepLayers P{};
