@@ -312,6 +312,18 @@ Step2List step2_list(const kvs_batch* b, const std::vector<int>& members, int sh
     return out;
 }
 
+// The list's work in planes, spread evenly over the 256 CUs (no span is less).
+long long step2_even_span(const kvs_batch* b, const std::vector<int>& members, int shape, int most) {
+    long long total = 0;
+    for (int i : members) {
+        const kvs_grid& g = b->inst[(size_t)i]->grid;
+        const long long xy = (long long)overlap_tiles((int)g.nx, 64 * kStep2Wx[shape]) * overlap_tiles((int)g.ny, kStep2Rows[shape]);
+        const int chunk = step2_chunk(g.nz, most), np = (int)g.nz - 2;
+        total += xy * (np + 3 * ((np + chunk - 1) / chunk));
+    }
+    return (total + 255) / 256;
+}
+
 // FORCE: some instance's envelope is non-zero in one of the two steps; the
 // others take the tile without force.
 template <bool VISC, bool FORCE, int WX, int R>
@@ -391,9 +403,13 @@ void step2_plan_work(kvs_batch* b, std::vector<int4>& work) {
                 if ((only >= 0 && step2_offers(only, g.ny) ? only : step2_shape(g)) == sh) p.members.push_back(i);
             }
             if (p.members.empty()) continue;
-            for (int m : {8, 12, 16, 24, 32, 48, 64, 96, 128}) {
+            // shorter segments have more planes to start and can only end earlier
+            // while their work spread evenly does: not even listed otherwise (the
+            // lists of 64 instances of edges 96 to 192 took 4 ms)
+            for (int m : {128, 96, 64, 48, 32, 24, 16, 12, 8}) {
+                if (p.most > 0 && step2_even_span(b, p.members, sh, m) > p.list.span) break;
                 Step2List l = step2_list(b, p.members, sh, m);
-                if (p.most == 0 || l.span < p.list.span) {
+                if (p.most == 0 || l.span <= p.list.span) {
                     p.list = std::move(l);
                     p.most = m;
                 }
