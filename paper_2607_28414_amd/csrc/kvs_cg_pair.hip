@@ -33,9 +33,10 @@
 // behind q, so one barrier per plane orders both stages.  Loads are issued two
 // planes ahead into two named register sets (the march is unrolled by two), so
 // that no wait is for a load of the plane before.  The tiles are held to 64
-// registers, so that two blocks of 1024 threads share a CU: without the limit
-// (68) the sweeps take 65 + 129 us at 256^3 instead of 60 + 120 (at 384 x 384 x 512
-// 238 + 680 instead of 260 + 722).
+// registers, so that two blocks of 1024 threads share a CU: without the limit the
+// update takes 68 to 72 and both sweeps are planned for one, 65 + 129 us at 256^3
+// instead of 60 + 120, 27 + 50 instead of 29 + 48 at 160 x 144 x 208, 37 + 83 instead
+// of 39 + 77 at 240 x 200 x 200; but 238 + 680 instead of 260 + 722 at 384 x 384 x 512.
 //
 // Measured at 256^3: 60 us (sums; 134 MB algorithmic, 156 MB fetched, mostly from
 // the 256 MB cache: LDS and FP64 issue bound it) + 120 us (update; 537 MB
