@@ -70,8 +70,8 @@ def test_ragged_batches_match_one_step_bitwise(kvs, dims, eta):
 
 @pytest.mark.parametrize("dims,eta", BATCHES[:2], ids=lambda v: str(v))
 def test_pairs_of_small_ragged_batches_are_no_slower(kvs, dims, eta):
-    """Measured 0.7 to 0.9 of the one-step launches; with a launch per shape it
-    was 1.1 to 2.2."""
+    """Measured 0.77 and 0.55 of the one-step launches; with a launch per shape it
+    was 1.67 and 1.06."""
     print(f"case ragged batch timing {dims}", flush=True)
     _, one = run(kvs, dims, eta, 1, (200,))
     _, two = run(kvs, dims, eta, 2, (200,))
